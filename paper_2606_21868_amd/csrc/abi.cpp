@@ -488,6 +488,13 @@ wisp_status poison_slots(wisp_ctx* c, int32_t layer, const std::vector<std::pair
   return WISP_OK;
 }
 
+// Token batches whose FFN runs as grouped GEMMs (a batch too long for the kernels' 32-bit offsets stays on the
+// per-item kernels where it ran on them before).
+bool batch_gemm(const wisp_ctx* c, int32_t T) {
+  return T >= kGroupedMinTokens &&
+         (grouped_supported(c->shape, c->desc.has_shared) || grouped_f32_supported(c->shape, T, c->desc.top_k));
+}
+
 // The fills of chunk ci on the side stream, in two halves with an event each (fill_ev[2 ci + h]).
 // With several chunks in a layer-step, a fill waits only for the part of the previous chunk's compute
 // that read its victim slot: that chunk's hits and first half (chunk_ev[2 (ci - 1)]) or its second
@@ -517,7 +524,7 @@ wisp_status issue_fills(wisp_ctx* c, int32_t layer, size_t ci) {
   std::vector<std::pair<int32_t, int32_t>> fills[2];
   for (size_t i = 0; i < cp.experts.size(); ++i)
     if (cp.fault[i]) fills[late[i]].push_back({cp.experts[i], cp.slots[i]});
-  const bool batch = L.T >= kGroupedMinTokens && grouped_supported(c->shape, c->desc.has_shared);
+  const bool batch = batch_gemm(c, L.T);
   for (int h = 0; h < (nch > 1 ? 2 : 1); ++h) {   // a single chunk has one half
     if (ci == 0) {
       if (h == 0 && L.use_ev_recorded) WISP_HIP(hipStreamWaitEvent(c->side, L.use_ev, 0), "hipStreamWaitEvent(use)");
@@ -595,6 +602,41 @@ wisp_status run_ffn(wisp_ctx* c, const std::vector<Work>& work, const void* x, h
     }
   }
   return flush();
+}
+
+// Grouped GEMMs of a token batch over a list of (expert, blob) in launches of up to kMaxGroups experts, from
+// the device pair order d_perm; expert -1 is the shared expert (every token, rows after the routed pairs).
+// cnt / off: pairs per expert and the first row of each in the order.
+wisp_status run_grouped(wisp_ctx* c, const std::vector<std::pair<int32_t, const uint8_t*>>& list, const void* x,
+                        int32_t T, const std::vector<int32_t>& cnt, const std::vector<int32_t>& off, hipStream_t st) {
+  const BlobLayout& B = c->blob;
+  const int k = c->k();
+  const uint64_t dI = static_cast<uint64_t>(B.d) * B.I;
+  const uint64_t nb = B.w_dtype == DT_FP8 ? static_cast<uint64_t>(B.d / 128) * (B.I / 128) * 2 : 0;
+  const bool f32_out = !grouped_supported(c->shape, c->desc.has_shared);
+  for (size_t g0 = 0; g0 < list.size(); g0 += kMaxGroups) {
+    GroupedBatch gb{};
+    gb.n_groups = static_cast<int32_t>(std::min<size_t>(kMaxGroups, list.size() - g0));
+    gb.shared = -1;
+    uint64_t nrows = 0;
+    for (int g = 0; g < gb.n_groups; ++g) {
+      const int32_t e = list[g0 + g].first;
+      gb.w[g] = list[g0 + g].second;
+      gb.row_off[g] = e < 0 ? T * k : off[e];
+      gb.rows[g] = e < 0 ? T : cnt[e];
+      if (e < 0) gb.shared = g;
+      nrows += static_cast<uint64_t>(gb.rows[g]);
+    }
+    const uint64_t ng = static_cast<uint64_t>(gb.n_groups);
+    LaunchTiming t1 = timing_begin(c, WISP_K_GROUPED_GATEUP);
+    WISP_HIP(launch_grouped_gateup(gb, c->shape, x, T, c->d_perm, k, c->h, f32_out, st, t1), "grouped gate/up launch");
+    timing_end(c, t1, WISP_K_GROUPED_GATEUP, ng * (2 * dI * B.elem + 2 * nb) + nrows * (B.d + B.I) * 2, nrows * 2 * 2 * dI);
+    LaunchTiming t2 = timing_begin(c, WISP_K_GROUPED_DOWN);
+    WISP_HIP(launch_grouped_down(gb, c->shape, c->h, T, c->d_perm, k, c->buf, f32_out, st, t2), "grouped down launch");
+    timing_end(c, t2, WISP_K_GROUPED_DOWN, ng * (dI * B.elem + nb) + nrows * (B.I * 2 + B.d * (f32_out ? 4 : 2)),
+               nrows * 2 * dI);
+  }
+  return WISP_OK;
 }
 
 // Speculative prefetch of ids[0..n) into `layer`'s slots (host pager).  Validated by the caller.
@@ -1046,7 +1088,7 @@ wisp_status wisp_route_topk(wisp_ctx* ctx, int32_t layer, const void* x_dev, int
     const int n = T * d.top_k;
     // a token batch for the grouped FFN: its pairs are ordered by expert now, from the device ids,
     // while the host waits for the ids and pages the layer in (after the last reader of the order)
-    const bool early = T >= kGroupedMinTokens && grouped_supported(ctx->shape, d.has_shared);
+    const bool early = batch_gemm(ctx, T);
     if (early) {
       ctx->perm_layer = -1;
       if (ctx->perm_use_recorded) WISP_HIP(hipStreamWaitEvent(st, ctx->perm_use_ev, 0), "hipStreamWaitEvent(perm use)");
@@ -1178,7 +1220,7 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
   }
   off[0] = 0;
   for (int e = 0; e < N; ++e) off[e + 1] = off[e] + cnt[e];
-  const bool grouped = T >= kGroupedMinTokens && grouped_supported(ctx->shape, ctx->desc.has_shared);
+  const bool grouped = batch_gemm(ctx, T);
   if (L.from_counts && (!grouped || ctx->perm_layer != layer || ctx->perm_T != T))
     return fail(WISP_E_STATE, "a page-in from device counts needs its layer's device permutation");
   if (!grouped) {   // the per-item launches list their pairs; the grouped ones read the device order
@@ -1226,42 +1268,6 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
       timing_end(ctx, tp, WISP_K_PERMUTE, static_cast<uint64_t>(n_pairs) * 8);
     }
   }
-  const BlobLayout& B = ctx->blob;
-  const uint64_t dI = static_cast<uint64_t>(B.d) * B.I;
-  // grouped GEMMs over a list of (expert, slot) in launches of up to kMaxGroups experts
-  auto run_grouped = [&](const std::vector<std::pair<int32_t, const uint8_t*>>& list) -> wisp_status {
-    for (size_t g0 = 0; g0 < list.size(); g0 += kMaxGroups) {
-      GroupedBatch gb;
-      gb.n_groups = static_cast<int32_t>(std::min<size_t>(kMaxGroups, list.size() - g0));
-      int32_t tiles = 0;
-      uint64_t nrows = 0;
-      for (int g = 0; g < gb.n_groups; ++g) {
-        const int32_t e = list[g0 + g].first;
-        gb.w[g] = list[g0 + g].second;
-        gb.row_off[g] = off[e];
-        gb.rows[g] = cnt[e];
-        tiles += grouped_row_tiles(cnt[e]);
-        gb.tile_end[g] = tiles;
-        nrows += static_cast<uint64_t>(cnt[e]);
-      }
-      for (int g = gb.n_groups; g < kMaxGroups; ++g) {
-        gb.w[g] = nullptr;
-        gb.row_off[g] = gb.rows[g] = 0;
-        gb.tile_end[g] = tiles;
-      }
-      const uint64_t ng = static_cast<uint64_t>(gb.n_groups);
-      LaunchTiming t1 = timing_begin(ctx, WISP_K_GROUPED_GATEUP);
-      WISP_HIP(launch_grouped_gateup(gb, ctx->shape, x_dev, T, ctx->d_perm, k, ctx->h, sm, t1), "grouped gate/up launch");
-      timing_end(ctx, t1, WISP_K_GROUPED_GATEUP, ng * 2 * dI * B.elem + nrows * (B.d + B.I) * 2,
-                 nrows * 2 * 2 * dI);
-      LaunchTiming t2 = timing_begin(ctx, WISP_K_GROUPED_DOWN);
-      WISP_HIP(launch_grouped_down(gb, ctx->shape, ctx->h, T, ctx->d_perm, k, reinterpret_cast<uint16_t*>(ctx->buf), sm,
-                                   t2),
-               "grouped down launch");
-      timing_end(ctx, t2, WISP_K_GROUPED_DOWN, ng * dI * B.elem + nrows * (B.I * 2 + B.d * 2), nrows * 2 * dI);
-    }
-    return WISP_OK;
-  };
   auto work_of = [&](int32_t e, const uint8_t* w) {
     Work wk;
     wk.w = w;
@@ -1315,11 +1321,12 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
       std::vector<std::pair<int32_t, const uint8_t*>> hits, faults[2];
       for (size_t i = 0; i < cp.experts.size(); ++i)
         (cp.fault[i] ? faults[L.late[ci][i]] : hits).push_back({cp.experts[i], L.chunk_ptrs[ci][i]});
-      if (!hits.empty() && (s = run_grouped(hits)) != WISP_OK) return s;
+      if (ci == 0 && ctx->desc.has_shared) hits.push_back({-1, L.shared_dev});
+      if (!hits.empty() && (s = run_grouped(ctx, hits, x_dev, T, cnt, off, sm)) != WISP_OK) return s;
       for (int h = 0; h < 2; ++h) {
         if (!faults[h].empty()) {
           WISP_HIP(hipStreamWaitEvent(sm, L.fill_ev[2 * ci + h], 0), "hipStreamWaitEvent(fill)");
-          if ((s = run_grouped(faults[h])) != WISP_OK) return s;
+          if ((s = run_grouped(ctx, faults[h], x_dev, T, cnt, off, sm)) != WISP_OK) return s;
         }
         if (nch > 1) WISP_HIP(hipEventRecord(L.chunk_ev[2 * ci + h], sm), "hipEventRecord(chunk)");
       }
@@ -1343,7 +1350,7 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
       }
     }
   }
-  if (grouped) {   // the grouped GEMMs leave bf16 expert outputs (no shared expert on this path)
+  if (grouped && grouped_supported(ctx->shape, ctx->desc.has_shared)) {   // bf16 expert outputs, no shared expert
     LaunchTiming tc = timing_begin(ctx, WISP_K_COMBINE);
     WISP_HIP(launch_combine_bf16(T, k, ctx->desc.d_model, w_dev, reinterpret_cast<const uint16_t*>(ctx->buf), y_dev, sm,
                                  tc),
@@ -1519,8 +1526,7 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
   }
   // a token batch for the grouped FFN pages in from the device's per-expert counts (no prefetch
   // bookkeeping needs its ids)
-  const bool batch_counts = T >= kGroupedMinTokens && grouped_supported(ctx->shape, d.has_shared) &&
-                            ctx->pf_mode == WISP_PREFETCH_OFF && ctx->cap >= 1;
+  const bool batch_counts = batch_gemm(ctx, T) && ctx->pf_mode == WISP_PREFETCH_OFF && ctx->cap >= 1;
   for (int32_t l = 0; l < d.n_layers; ++l) {
     const void* xl = static_cast<const uint8_t*>(x_dev) + l * xs;
     int32_t* il = idx_dev + static_cast<size_t>(l) * T * d.top_k;
@@ -1733,6 +1739,24 @@ wisp_status wisp_offload_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32
       base = o.staging[b];
       WISP_HIP(hipStreamWaitEvent(sm, o.filled[b], 0), "hipStreamWaitEvent(staging fill)");
     }
+    if (batch_gemm(ctx, T) && !grouped_supported(ctx->shape, d.has_shared)) {
+      // the pager's grouped GEMMs, over the pair order wisp_route_topk enqueued on this stream
+      std::vector<int32_t>& cnt = ctx->e_cnt;
+      std::vector<int32_t>& off = ctx->e_off;
+      std::fill(cnt.begin(), cnt.end(), 0);
+      for (int32_t p = 0; p < T * k; ++p) ++cnt[ids[p]];
+      off[0] = 0;
+      std::vector<std::pair<int32_t, const uint8_t*>> list;
+      for (int e = 0; e < d.n_experts; ++e) {
+        off[e + 1] = off[e] + cnt[e];
+        if (cnt[e] > 0) list.push_back({e, base + static_cast<size_t>(e) * ctx->master_stride});
+      }
+      if (d.has_shared) list.push_back({-1, ctx->layers[l].shared_dev});
+      ctx->perm_layer = -1;
+      if ((s = run_grouped(ctx, list, xl, T, cnt, off, sm)) != WISP_OK) return s;
+      WISP_HIP(hipEventRecord(ctx->perm_use_ev, sm), "hipEventRecord(perm use)");
+      ctx->perm_use_recorded = true;
+    } else {
     // the routed experts of the layer, ascending, each with its (token, rank) pairs
     std::vector<Work> work;
     for (int e = 0; e < d.n_experts; ++e) {
@@ -1751,6 +1775,7 @@ wisp_status wisp_offload_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32
       work.push_back(std::move(wk));
     }
     if ((s = run_ffn(ctx, work, xl, sm)) != WISP_OK) return s;
+    }
     LaunchTiming tc = timing_begin(ctx, WISP_K_COMBINE);
     WISP_HIP(launch_combine(T, k, d.d_model, d.has_shared, wl, ctx->buf, yl, sm, tc), "combine launch");
     timing_end(ctx, tc, WISP_K_COMBINE, 0);

@@ -462,8 +462,6 @@ bool grouped_supported(const FfnShape& s, int has_shared) {
          s.blob.d % kBR == 0 && s.blob.I % (kBR / 2) == 0;   // whole column tiles and K stages
 }
 
-int grouped_row_tiles(int rows) { return (rows + kRB - 1) / kRB; }
-
 namespace {
 // the buffer loads address x, h and an expert's weights by 32-bit byte offsets below kOutOfRange
 bool offsets_fit(const FfnShape& s, int n_tok, int k) {
@@ -497,7 +495,6 @@ hipError_t launch_permute_pairs(const int32_t* idx, int n_pairs, int N, int32_t*
   return hipGetLastError();
 }
 
-namespace {
 int compute_units() {
   static int cus = 0;
   if (!cus) {
@@ -510,28 +507,40 @@ int compute_units() {
   }
   return cus;
 }
-}  // namespace
+
+bool grouped_f32_supported(const FfnShape& s, int T, int k) {
+  // (bf16 widths are multiples of 64 and fp8 widths of 128: whole stages and whole waves' columns)
+  return s.x_dtype == DT_BF16 && s.h_dtype == DT_BF16 && s.blob.bytes < kOutOfRange &&
+         offsets_fit(s, T, k) && static_cast<uint64_t>(T) * (k + 1) * s.blob.I * 2 < kOutOfRange;
+}
 
 hipError_t launch_grouped_gateup(const GroupedBatch& b, const FfnShape& s, const void* x, int n_tok,
-                                 const int32_t* perm, int k, void* hs, hipStream_t st, const LaunchTiming& tm) {
+                                 const int32_t* perm, int k, void* hs, bool f32_out, hipStream_t st, const LaunchTiming& tm) {
   if (b.n_groups <= 0) return hipSuccess;
-  if (b.n_groups > kMaxGroups || !grouped_supported(s, 0) || !offsets_fit(s, n_tok, k)) return hipErrorInvalidValue;
-  const int tiles = b.tile_end[b.n_groups - 1] * (s.blob.I / (kBR / 2));
+  if (b.n_groups > kMaxGroups || !offsets_fit(s, n_tok, k)) return hipErrorInvalidValue;
   const uint32_t x_bytes = static_cast<uint32_t>(n_tok) * s.blob.d * 2;
+  if (f32_out) return launch_tile_gateup(b, s, x, x_bytes, perm, k, hs, st, tm);
+  GroupedBatch gb = b;
+  int nb = 0;
+  for (int g = 0; g < b.n_groups; ++g) gb.tile_end[g] = nb += (b.rows[g] + kRB - 1) / kRB;
+  const int tiles = nb * (s.blob.I / (kBR / 2));
   hipExtLaunchKernelGGL(grouped_kernel<MODE_UP>, dim3(std::min(tiles, compute_units())), dim3(512), 0, st, tm.start,
-                        tm.stop, 0, b, static_cast<const uint16_t*>(x), x_bytes, perm, k, s.blob.d, s.blob.I, hs);
+                        tm.stop, 0, gb, static_cast<const uint16_t*>(x), x_bytes, perm, k, s.blob.d, s.blob.I, hs);
   return hipGetLastError();
 }
 
 hipError_t launch_grouped_down(const GroupedBatch& b, const FfnShape& s, const void* hs, int n_tok, const int32_t* perm,
-                               int k, uint16_t* buf, hipStream_t st, const LaunchTiming& tm) {
+                               int k, void* buf, bool f32_out, hipStream_t st, const LaunchTiming& tm) {
   if (b.n_groups <= 0) return hipSuccess;
-  if (b.n_groups > kMaxGroups || !grouped_supported(s, 0) || !offsets_fit(s, n_tok, k)) return hipErrorInvalidValue;
-  const int tiles = b.tile_end[b.n_groups - 1] * (s.blob.d / kBR);
-  const uint32_t hs_bytes = static_cast<uint32_t>(n_tok) * k * s.blob.I * 2;
+  if (b.n_groups > kMaxGroups || !offsets_fit(s, n_tok, k)) return hipErrorInvalidValue;
+  const uint32_t hs_bytes = static_cast<uint32_t>(n_tok) * (f32_out ? k + 1 : k) * s.blob.I * 2;
+  if (f32_out) return launch_tile_down(b, s, hs, hs_bytes, perm, k, static_cast<float*>(buf), st, tm);
+  GroupedBatch gb = b;
+  int nb = 0;
+  for (int g = 0; g < b.n_groups; ++g) gb.tile_end[g] = nb += (b.rows[g] + kRB - 1) / kRB;
+  const int tiles = nb * (s.blob.d / kBR);
   hipExtLaunchKernelGGL(grouped_kernel<MODE_DN>, dim3(std::min(tiles, compute_units())), dim3(512), 0, st, tm.start,
-                        tm.stop, 0, b, static_cast<const uint16_t*>(hs), hs_bytes, perm, k, s.blob.d, s.blob.I,
-                        static_cast<void*>(buf));
+                        tm.stop, 0, gb, static_cast<const uint16_t*>(hs), hs_bytes, perm, k, s.blob.d, s.blob.I, buf);
   return hipGetLastError();
 }
 

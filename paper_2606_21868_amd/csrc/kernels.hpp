@@ -97,18 +97,22 @@ hipError_t launch_combine_bf16(int T, int k, int d, const float* w, const uint16
 // Token batches (prefill): grouped GEMMs on the matrix cores over slot-indirected experts.
 // The (token, rank) pairs p = t*k + j are ordered by expert (stable); expert g of a launch owns
 // rows [row_off, row_off + rows) of that order.  Up to kMaxGroups experts per launch (the batch is a
-// 2.5 KB kernel argument).
-constexpr int kMaxGroups = 128;
+// 2.9 KB kernel argument: 128 routed experts and a shared one still go in one launch).
+constexpr int kMaxGroups = 144;
 constexpr int kGroupedMinTokens = 16;   // token batches from this size take the grouped GEMMs
 struct GroupedBatch {
   const uint8_t* w[kMaxGroups];   // the expert's blob in its HBM slot
   int32_t row_off[kMaxGroups];    // first row of the expert in the expert-sorted pair order
   int32_t rows[kMaxGroups];       // pairs routed to the expert (>= 1)
-  int32_t tile_end[kMaxGroups];   // cumulative row-tile counts (grouped_row_tiles)
+  int32_t tile_end[kMaxGroups];   // cumulative row-block counts (filled by the launch)
   int32_t n_groups;
+  int32_t shared;                 // the group that is the shared expert (row r: token r, rank k), or -1
 };
+// The shapes whose token batches keep bf16 expert outputs (bf16 weights, d a multiple of 256 and I of 128, no
+// shared expert), and those whose grouped GEMMs (tile_gemm.hip) keep them in fp32, as the per-item kernels do:
+// fp8 weights, other widths, a shared expert.
 bool grouped_supported(const FfnShape& s, int has_shared);
-int grouped_row_tiles(int rows);
+bool grouped_f32_supported(const FfnShape& s, int T, int k);
 // perm[off_e + i] = the i-th pair (ascending) routed to expert e; off_e = pairs of experts < e.
 // counts: device scratch of permute_segments(n_pairs) * N int32.  If totals is not NULL (N words of
 // host-coherent memory), totals[e] = seq << 32 | pairs routed to e, each written by one atomic store.
@@ -116,13 +120,19 @@ int permute_segments(int n_pairs);
 hipError_t launch_permute_pairs(const int32_t* idx, int n_pairs, int N, int32_t* perm, int32_t* counts, hipStream_t st,
                                 const LaunchTiming& tm, uint64_t* totals = nullptr, uint32_t seq = 0);
 // hs[row] = bf16(silu(W1 x[t]) * (W3 x[t])) for every row of the batch's experts (row in sorted order);
-// x holds n_tok token rows, hs n_tok * k pair rows.
+// x holds n_tok token rows, hs n_tok * k pair rows (the shared expert's n_tok rows follow them).
 hipError_t launch_grouped_gateup(const GroupedBatch& b, const FfnShape& s, const void* x, int n_tok,
-                                 const int32_t* perm, int k, void* hs, hipStream_t st, const LaunchTiming& tm);
-// buf[t*(k+1)+j] = bf16(W2 hs[row]) for the pair p = t*k+j of every row (bf16, as h is: the combine
-// reads half the bytes).
+                                 const int32_t* perm, int k, void* hs, bool f32_out, hipStream_t st, const LaunchTiming& tm);
+// buf[t*(k+1)+j] = W2 hs[row] for the pair p = t*k+j of every row: bf16, as h is (the combine reads half
+// the bytes), or fp32 with f32_out.
 hipError_t launch_grouped_down(const GroupedBatch& b, const FfnShape& s, const void* hs, int n_tok, const int32_t* perm,
-                               int k, uint16_t* buf, hipStream_t st, const LaunchTiming& tm);
+                               int k, void* buf, bool f32_out, hipStream_t st, const LaunchTiming& tm);
+
+hipError_t launch_tile_gateup(const GroupedBatch& b, const FfnShape& s, const void* x, uint32_t x_bytes,
+                              const int32_t* perm, int k, void* hs, hipStream_t st, const LaunchTiming& tm);
+hipError_t launch_tile_down(const GroupedBatch& b, const FfnShape& s, const void* hs, uint32_t hs_bytes,
+                            const int32_t* perm, int k, float* buf, hipStream_t st, const LaunchTiming& tm);
+int compute_units();   // of the current device
 
 // Router: logits[t, e] = W_r[e] . x[t] (fp32 accumulate), written as *n_split partial sums over column
 // slices (slice s at logits + s * T * N; 1 for decode sizes, at most kRouterMaxSplit), which the
