@@ -163,7 +163,7 @@ struct wisp_ctx {
   uint32_t* d_stats = nullptr;       // [L][2] hits, misses of the current step
   uint32_t* h_stats = nullptr;       // pinned copy
   bool fusion = true;                // fused decode kernels (route + page; down + combine)
-  uint64_t* d_logit_tags = nullptr;  // [4][N] tagged logit words of the one-launch router kernels
+  uint64_t* d_logit_tags = nullptr;  // [kRouteSelectTokens][N] tagged logit words of the one-launch router kernels
   uint32_t logit_tag = 0;            // tag of the last such launch (never 0)
   // speculative prefetch inside wisp_decode_step (host pager)
   int32_t pf_mode = WISP_PREFETCH_OFF;
@@ -804,9 +804,10 @@ wisp_status wisp_create(const wisp_model_desc* desc, wisp_ctx** out) {
   c->e_cnt.assign(N, 0);
   c->e_off.assign(N + 1, 0);
   c->pf_mark.assign(N, 0);
-  if (hipMalloc(&p, sizeof(uint64_t) * 4 * N) != hipSuccess) return bail(WISP_E_NOMEM, "scratch");
+  const size_t tag_bytes = sizeof(uint64_t) * kRouteSelectTokens * N;
+  if (hipMalloc(&p, tag_bytes) != hipSuccess) return bail(WISP_E_NOMEM, "scratch");
   c->d_logit_tags = static_cast<uint64_t*>(p);
-  if (hipMemset(c->d_logit_tags, 0, sizeof(uint64_t) * 4 * N) != hipSuccess)
+  if (hipMemset(c->d_logit_tags, 0, tag_bytes) != hipSuccess)
     return bail(WISP_E_HIP, "hipMemset(logit tags)");
 
   c->pair_order.resize(static_cast<size_t>(T) * k);
@@ -1033,13 +1034,13 @@ wisp_status wisp_set_pager(wisp_ctx* ctx, int32_t pager) {
 }
 
 namespace {
-// The router launches of a layer-step: logits and selection (one launch for T <= 4 with fusion on).
+// The router launches of a layer-step: logits and selection (one launch for few tokens with fusion on).
 // With idx_tagged, the selection also writes each id to host-coherent memory as a word tagged seq.
 wisp_status route_kernels(wisp_ctx* ctx, LayerState& L, const void* x_dev, int32_t T, int32_t* idx_dev, float* w_dev,
                           uint64_t* idx_tagged, uint32_t seq, hipStream_t st) {
   const auto& d = ctx->desc;
-  if (ctx->fusion && T <= 4) {
-    // logits and selection in one launch (the first workgroup selects once every row is published)
+  if (ctx->fusion && T <= kRouteSelectTokens && (T + 3) / 4 <= d.n_experts) {
+    // logits and selection in one launch (a workgroup per four tokens selects once every row is published)
     LaunchTiming t1 = timing_begin(ctx, WISP_K_ROUTER_SELECT);
     WISP_HIP(launch_route_select(L.wr, x_dev, d.x_dtype, d.d_model, ctx->d_logit_tags, next_logit_tag(ctx),
                                  T, d.n_experts,

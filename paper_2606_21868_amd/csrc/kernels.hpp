@@ -142,11 +142,12 @@ hipError_t launch_router_logits(const float* wr, const void* x, int x_dtype, int
                                 int* n_split, hipStream_t st, const LaunchTiming& tm);
 // Router selection: idx/w [T, k] by routing variant.  If idx_host is given, entry t*k+j of it (in
 // host-coherent memory) also receives (seq << 32 | id) as one 64-bit store.
-// Decode (T <= 4): router logits and selection in one launch (workgroup 0 selects once every row is
-// published); the same ids, gates and tagged ids as launch_router_logits + launch_router_select.
-// logits: [T, N] 64-bit words (at least 4 x N) where the rows are published tagged with `tag`, which
+// Decode (T <= kRouteSelectTokens, ceil(T / 4) <= N): router logits and selection in one launch (a workgroup per
+// four tokens selects once every row is published); the same ids, gates and tagged ids as
+// launch_router_logits + launch_router_select.  logits: [T, N] 64-bit words where the rows are published tagged with `tag`, which
 // must differ from the tag of the launch that last wrote them (a per-launch sequence number, never 0;
 // the words start at 0).
+constexpr int kRouteSelectTokens = 8;
 hipError_t launch_route_select(const float* wr, const void* x, int x_dtype, int d, uint64_t* logits, uint32_t tag,
                                int T, int N, int k, int route, int n_groups, int topk_groups,
                                int32_t* idx, float* w, uint64_t* idx_host, uint32_t seq, hipStream_t st,

@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(256) select_page_kernel(
 // store each); workgroup 0, which has loaded the slot table into registers before its row, then runs the
 // selection and the pager on the complete logits, reading each word until it carries this launch's tag.
 // The other workgroups wait for nothing.
-template <int XT>
+template <int XT, int NT>
 __global__ void __launch_bounds__(256) route_page_kernel(
     const float* __restrict__ wr, const void* __restrict__ x, int d, uint64_t* __restrict__ logits, uint32_t tag,
     int T, int N, int k, int route, int n_groups, int topk_groups,
@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(256) route_page_kernel(
   __shared__ float part[4][4];
   const int e = blockIdx.x;
   if (e != 0) {
-    const float z = router_row<XT>(wr, x, 0, T, d, e, part);
+    const float z = router_row<XT, NT>(wr, x, 0, T, d, e, part);
     if (static_cast<int>(threadIdx.x) < T)
       __hip_atomic_store(logits + static_cast<size_t>(threadIdx.x) * N + e, tag_logit(tag, z), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
@@ -239,7 +239,7 @@ __global__ void __launch_bounds__(256) route_page_kernel(
   // the table goes into registers first (its loads do not depend on the routing), the row loads follow
   // without waiting for it
   const TableRegs tab = load_table_regs(N, C, pi, pinv, tau, clock, slot_ptr);
-  const float z = router_row<XT>(wr, x, 0, T, d, e, part);
+  const float z = router_row<XT, NT>(wr, x, 0, T, d, e, part);
   if (static_cast<int>(threadIdx.x) < T)
     __hip_atomic_store(logits + static_cast<size_t>(threadIdx.x) * N + e, tag_logit(tag, z), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
@@ -260,14 +260,10 @@ hipError_t launch_route_page(const float* wr, const void* x, int x_dtype, int d,
   if (T < 1 || T > 4 || N > 256 || C > 256 || k > 8 || T * k > 32 || T * k > C || d % 4 != 0 ||
       T * k + (has_shared ? 1 : 0) > kMaxItems)
     return hipErrorInvalidValue;
-  if (x_dtype == DT_F32)
-    hipExtLaunchKernelGGL(route_page_kernel<DT_F32>, dim3(N), dim3(256), 0, st, tm.start, tm.stop, 0, wr, x, d, logits,
-                          tag, T, N, k, route, n_groups, topk_groups, idx, w, pi, pinv, tau, clock, C, slot_ptr,
-                          master_base, master_stride, shared_dev, has_shared, plan, stats);
-  else
-    hipExtLaunchKernelGGL(route_page_kernel<DT_BF16>, dim3(N), dim3(256), 0, st, tm.start, tm.stop, 0, wr, x, d,
-                          logits, tag, T, N, k, route, n_groups, topk_groups, idx, w, pi, pinv, tau, clock, C,
-                          slot_ptr, master_base, master_stride, shared_dev, has_shared, plan, stats);
+  auto kern = WISP_ROUTER_ROW_KERNEL(route_page_kernel, x_dtype == DT_F32, T);
+  hipExtLaunchKernelGGL(kern, dim3(N), dim3(256), 0, st, tm.start, tm.stop, 0, wr, x, d, logits, tag, T, N, k, route,
+                        n_groups, topk_groups, idx, w, pi, pinv, tau, clock, C, slot_ptr, master_base, master_stride,
+                        shared_dev, has_shared, plan, stats);
   return hipGetLastError();
 }
 
