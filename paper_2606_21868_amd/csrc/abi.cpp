@@ -488,6 +488,24 @@ wisp_status poison_slots(wisp_ctx* c, int32_t layer, const std::vector<std::pair
   return WISP_OK;
 }
 
+// Few tokens, whose FFN streams every expert once (stream_gemm.hip), with either pager: fp8 weights, and bf16 from two
+// tokens (one token has the single-token kernels).  us per launch, gate/up + down, against the per-item
+// kernels: fp8, one token (9 experts, d 7168) 42.7 + 24.1 against 57.4 + 36.7; bf16, seven tokens (50 experts, d 2048)
+// 46.9 + 24.7 against 59 + 33; four tokens (6 experts, d 4096) 174 + 92 against 211 + 133.
+bool stream_tokens(const wisp_ctx* c, int32_t T) {
+  return T >= (c->desc.w_dtype == WISP_FP8E4M3_B128 ? 1 : 2) && T <= kStreamMaxTokens && stream_supported(c->shape);
+}
+
+// Token batches with few rows per expert, streamed the same way from the device pair order instead of as grouped
+// GEMMs: bf16 weights, a mean of up to five rows.  us per pass, streamed against grouped: two layers of 128 experts,
+// d 2048, at 2.3 / 4 / 5 / 6.3 mean rows 423 / 490 / 537 / 612 against 543 / 562 / 569 / 570; 8 experts, d 4096,
+// at 4 / 5 / 7.8 rows 555 / 631 / 858 against 646 / 643 / 642.  fp8 rows cost the conversion of every code each:
+// 597 against 560 at two mean rows already.
+bool stream_rows_batch(const wisp_ctx* c, int32_t T) {
+  return c->desc.w_dtype == WISP_BF16 && stream_supported(c->shape) &&
+         static_cast<int64_t>(T) * c->k() <= 5 * static_cast<int64_t>(c->desc.n_experts);
+}
+
 // Token batches whose FFN runs as grouped GEMMs (a batch too long for the kernels' 32-bit offsets stays on the
 // per-item kernels where it ran on them before).
 bool batch_gemm(const wisp_ctx* c, int32_t T) {
@@ -563,8 +581,55 @@ uint64_t ffn_bytes(const wisp_ctx* c, const FfnBatch& b, bool gateup) {
 // kMaxItems items; the per-(token, rank) outputs land in buf.
 struct Pair { int32_t t, out; };
 struct Work { const uint8_t* w; std::vector<Pair> pairs; };
+struct StreamItem { const uint8_t* w; uint64_t at; int32_t rows; };   // StreamBatch
 
-wisp_status run_ffn(wisp_ctx* c, const std::vector<Work>& work, const void* x, hipStream_t st, bool down = true) {
+// The launches of a list of stream items (launch_stream_*), counted as the given kernel classes.
+wisp_status run_stream(wisp_ctx* c, const std::vector<StreamItem>& items, const void* x, const int32_t* perm,
+                       bool bf16_out, int k_up, int k_down, hipStream_t st) {
+  const BlobLayout& B = c->blob;
+  const uint64_t n = static_cast<uint64_t>(B.d) * B.I;
+  const uint64_t nb = B.w_dtype == DT_FP8 ? static_cast<uint64_t>(B.d / 128) * (B.I / 128) * 2 : 0;
+  for (size_t i0 = 0; i0 < items.size(); i0 += kMaxStreamItems) {
+    StreamBatch b;
+    b.n_items = static_cast<int32_t>(std::min<size_t>(kMaxStreamItems, items.size() - i0));
+    uint64_t nt = 0, nw = 0;   // token rows, distinct experts (the items of one follow each other)
+    for (int i = 0; i < b.n_items; ++i) {
+      const StreamItem& it = items[i0 + i];
+      b.w[i] = it.w;
+      b.at[i] = it.at;
+      b.rows[i] = static_cast<uint8_t>(it.rows);
+      nt += it.rows;
+      nw += i == 0 || items[i0 + i - 1].w != it.w ? 1 : 0;
+    }
+    LaunchTiming t1 = timing_begin(c, k_up);
+    WISP_HIP(launch_stream_gateup(b, c->shape, x, perm, c->k(), c->h, st, t1), "streamed gate/up launch");
+    timing_end(c, t1, k_up, nw * (2 * n * B.elem + 2 * nb) + nt * (B.d + B.I) * 2, nt * 4 * n);
+    LaunchTiming t2 = timing_begin(c, k_down);
+    WISP_HIP(launch_stream_down(b, c->shape, c->h, perm, c->k(), c->buf, bf16_out, st, t2), "streamed down launch");
+    timing_end(c, t2, k_down, nw * (n * B.elem + nb) + nt * (B.I * 2 + B.d * (bf16_out ? 2 : 4)), nt * 2 * n);
+  }
+  return WISP_OK;
+}
+
+// Items of up to kStreamRows pairs from work lists (tokens below 16).
+std::vector<StreamItem> stream_items(const std::vector<Work>& work, int rows_per_token) {
+  std::vector<StreamItem> items;
+  for (const Work& wk : work)
+    for (size_t p0 = 0; p0 < wk.pairs.size(); p0 += kStreamRows) {
+      StreamItem it{wk.w, 0, static_cast<int32_t>(std::min<size_t>(kStreamRows, wk.pairs.size() - p0))};
+      for (int q = 0; q < it.rows; ++q) {
+        const Pair& p = wk.pairs[p0 + q];
+        it.at |= static_cast<uint64_t>(p.t) << (4 * q) | static_cast<uint64_t>(p.out % rows_per_token) << (32 + 4 * q);
+      }
+      items.push_back(it);
+    }
+  return items;
+}
+
+wisp_status run_ffn(wisp_ctx* c, const std::vector<Work>& work, const void* x, int32_t T, hipStream_t st,
+                    bool down = true) {
+  if (stream_tokens(c, T))
+    return run_stream(c, stream_items(work, c->k() + 1), x, nullptr, false, WISP_K_FFN_GATEUP, WISP_K_FFN_DOWN, st);
   FfnBatch b;
   b.n_items = 0;
   b.max_ntok = 0;
@@ -614,6 +679,15 @@ wisp_status run_grouped(wisp_ctx* c, const std::vector<std::pair<int32_t, const 
   const uint64_t dI = static_cast<uint64_t>(B.d) * B.I;
   const uint64_t nb = B.w_dtype == DT_FP8 ? static_cast<uint64_t>(B.d / 128) * (B.I / 128) * 2 : 0;
   const bool f32_out = !grouped_supported(c->shape, c->desc.has_shared);
+  if (stream_rows_batch(c, T)) {
+    std::vector<StreamItem> items;
+    for (const auto& [e, w] : list) {
+      const int32_t n = e < 0 ? T : cnt[e], at = e < 0 ? 0 : off[e];
+      for (int32_t i = 0; i < n; i += kStreamRows)
+        items.push_back({w, static_cast<uint64_t>(at + i) | (e < 0 ? kStreamShared : 0), std::min(kStreamRows, n - i)});
+    }
+    return run_stream(c, items, x, c->d_perm, !f32_out, WISP_K_GROUPED_GATEUP, WISP_K_GROUPED_DOWN, st);
+  }
   for (size_t g0 = 0; g0 < list.size(); g0 += kMaxGroups) {
     GroupedBatch gb{};
     gb.n_groups = static_cast<int32_t>(std::min<size_t>(kMaxGroups, list.size() - g0));
@@ -1300,10 +1374,10 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
       all.rank[all.n_items] = k;
       ++all.n_items;
     }
-    if (!hits.empty() && (s = run_ffn(ctx, hits, x_dev, sm, false)) != WISP_OK) return s;
+    if (!hits.empty() && (s = run_ffn(ctx, hits, x_dev, T, sm, false)) != WISP_OK) return s;
     if (!faults.empty()) {
       WISP_HIP(hipStreamWaitEvent(sm, L.fill_ev[0], 0), "hipStreamWaitEvent(fill)");
-      if ((s = run_ffn(ctx, faults, x_dev, sm, false)) != WISP_OK) return s;
+      if ((s = run_ffn(ctx, faults, x_dev, T, sm, false)) != WISP_OK) return s;
     }
     FfnBatch b;
     b.n_items = all.n_items;
@@ -1341,11 +1415,11 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
         for (int32_t t = 0; t < T; ++t) wk.pairs.push_back({t, t * rows + k});
         hits.push_back(std::move(wk));
       }
-      if (!hits.empty() && (s = run_ffn(ctx, hits, x_dev, sm)) != WISP_OK) return s;
+      if (!hits.empty() && (s = run_ffn(ctx, hits, x_dev, T, sm)) != WISP_OK) return s;
       for (int h = 0; h < 2; ++h) {
         if (!faults[h].empty()) {
           WISP_HIP(hipStreamWaitEvent(sm, L.fill_ev[2 * ci + h], 0), "hipStreamWaitEvent(fill)");
-          if ((s = run_ffn(ctx, faults[h], x_dev, sm)) != WISP_OK) return s;
+          if ((s = run_ffn(ctx, faults[h], x_dev, T, sm)) != WISP_OK) return s;
         }
         if (nch > 1) WISP_HIP(hipEventRecord(L.chunk_ev[2 * ci + h], sm), "hipEventRecord(chunk)");
       }
@@ -1451,7 +1525,8 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
     hipStream_t sm = static_cast<hipStream_t>(stream);
     const int max_items = T * d.top_k + d.has_shared;
     const int C = ctx->cap;
-    const bool dc = ctx->fusion && T == 1 && down_combine_supported(ctx->shape);
+    const bool stream = stream_tokens(ctx, T);
+    const bool dc = !stream && ctx->fusion && T == 1 && down_combine_supported(ctx->shape);
     for (int32_t l = 0; l < d.n_layers; ++l) {
       LayerState& L = ctx->layers[l];
       if (!L.wr) return fail(WISP_E_STATE, "router weights not set for this layer");
@@ -1488,8 +1563,12 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
       }
       LaunchTiming t3 = timing_begin(ctx, WISP_K_FFN_GATEUP);
       LaunchTiming t4 = dc ? LaunchTiming{} : timing_begin(ctx, WISP_K_FFN_DOWN);
-      WISP_HIP(launch_ffn_dev(ctx->d_plan, max_items, ctx->shape, xl, ctx->h, ctx->buf, !dc, sm, t3, t4),
-               "device-planned FFN launch");
+      if (stream)
+        WISP_HIP(launch_stream_dev(ctx->d_plan, max_items, ctx->shape, xl, ctx->h, ctx->buf, sm, t3, t4),
+                 "device-planned FFN launch");
+      else
+        WISP_HIP(launch_ffn_dev(ctx->d_plan, max_items, ctx->shape, xl, ctx->h, ctx->buf, !dc, sm, t3, t4),
+                 "device-planned FFN launch");
       timing_end(ctx, t3, WISP_K_FFN_GATEUP, 0);
       if (!dc) timing_end(ctx, t4, WISP_K_FFN_DOWN, 0);
       if (dc) {
@@ -1775,7 +1854,7 @@ wisp_status wisp_offload_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32
       for (int32_t t = 0; t < T; ++t) wk.pairs.push_back({t, t * rows + k});
       work.push_back(std::move(wk));
     }
-    if ((s = run_ffn(ctx, work, xl, sm)) != WISP_OK) return s;
+    if ((s = run_ffn(ctx, work, xl, T, sm)) != WISP_OK) return s;
     }
     LaunchTiming tc = timing_begin(ctx, WISP_K_COMBINE);
     WISP_HIP(launch_combine(T, k, d.d_model, d.has_shared, wl, ctx->buf, yl, sm, tc), "combine launch");

@@ -22,6 +22,7 @@
 
 #include <algorithm>
 
+#include "blob_copy.hpp"
 #include "kernels.hpp"
 
 namespace wisp {
@@ -364,24 +365,7 @@ __global__ void __launch_bounds__(256) ffn_gateup_dev(const FfnBatch* __restrict
     rows_body<WT, IT, MODE_GATEUP, LPR, NLT>(it, it.src, const_cast<uint8_t*>(it.w), vin, d, d, I, r_begin,
                                              min(I, r_begin + rows), off1, off3, soff1, soff3, h, I, lds);
   } else if (j < fault_wgs + copy_wgs) {
-    // copy [copy_off, copy_off + copy_bytes) host -> slot, four 16-byte loads in flight per thread
-    const int q = j - fault_wgs;
-    const size_t n16 = copy_bytes / 16;
-    const size_t per = (n16 + copy_wgs - 1) / copy_wgs;
-    const size_t c0 = static_cast<size_t>(q) * per;
-    const size_t c1 = c0 + per < n16 ? c0 + per : n16;
-    const uint4* src = reinterpret_cast<const uint4*>(it.src + copy_off);
-    uint4* dst = reinterpret_cast<uint4*>(const_cast<uint8_t*>(it.w) + copy_off);
-    size_t i = c0 + threadIdx.x;
-    for (; i + 768 < c1; i += 1024) {
-      const uint4 a = src[i], b = src[i + 256], c = src[i + 512], e = src[i + 768];
-      dst[i] = a; dst[i + 256] = b; dst[i + 512] = c; dst[i + 768] = e;
-    }
-    for (; i < c1; i += 256) dst[i] = src[i];
-    if (q == copy_wgs - 1) {
-      for (size_t b = n16 * 16 + threadIdx.x; b < copy_bytes; b += 256)
-        const_cast<uint8_t*>(it.w)[copy_off + b] = it.src[copy_off + b];
-    }
+    copy_share(it.src, const_cast<uint8_t*>(it.w), copy_off, copy_bytes, j - fault_wgs, copy_wgs);
   }
 }
 
@@ -664,7 +648,7 @@ RowsKernel pick_kernel(int lpr, int nl) {
   } else if constexpr (WT == DT_BF16) {
     WISP_K(64, 4) WISP_K(64, 8) WISP_K(32, 3) WISP_K(64, 28) WISP_K(32, 1) WISP_K(16, 1) WISP_K(16, 3)
   } else {
-    WISP_K(64, 7) WISP_K(64, 2) WISP_K(16, 1)
+    // (fp8 rows of few tokens are streamed, stream_gemm.hip)
   }
   // any other shape: runtime chunk count
   WISP_K(64, 0) WISP_K(32, 0) WISP_K(16, 0) WISP_K(8, 0)
@@ -863,14 +847,10 @@ hipError_t launch_ffn_dev(const FfnBatch* plan, int max_items, const FfnShape& s
   WISP_G(DT_BF16, DT_BF16, 64, 4)   // d = 2048
   WISP_G(DT_BF16, DT_BF16, 32, 1)   // d = 256
   WISP_G(DT_BF16, DT_BF16, 16, 3)   // d = 384
-  WISP_G(DT_FP8, DT_BF16, 64, 7)    // d = 7168
-  WISP_G(DT_FP8, DT_BF16, 16, 1)    // d = 256
   WISP_G(DT_F32, DT_F32, 64, 1)     // d = 256
   WISP_DD(DT_BF16, DT_BF16, 32, 3)  // I = 768
   WISP_DD(DT_BF16, DT_BF16, 16, 1)  // I = 128
   WISP_DD(DT_BF16, DT_BF16, 8, 3)   // I = 192
-  WISP_DD(DT_FP8, DT_BF16, 64, 2)   // I = 2048
-  WISP_DD(DT_FP8, DT_BF16, 16, 1)   // I = 256
   WISP_DD(DT_F32, DT_F32, 64, 2)    // I = 512
 #undef WISP_G
 #undef WISP_DD

@@ -79,6 +79,31 @@ hipError_t launch_down_combine_dev(const FfnBatch* plan, int max_items, const Ff
                                    const float* gates, float* y, int k, int has_shared, hipStream_t st,
                                    const LaunchTiming& tm);
 
+// Few token rows per expert: every expert of a launch streamed once for up to kStreamRows of its rows
+// (stream_gemm.hip; an expert with more rows takes several items).  An item's rows are (token, rank) pairs: without
+// perm, packed in at (token of row i at bits 4 i, rank at bits 32 + 4 i: up to kStreamMaxTokens tokens); with
+// perm (the sorted pair order), perm[at .. at + rows), or, with kStreamShared, tokens at .. at + rows of the shared
+// expert.  h and buf rows are token * (k + 1) + rank, as for the per-item kernels; buf in fp32, or bf16 with bf16_out.
+constexpr int kStreamMaxTokens = 15;
+constexpr int kStreamRows = 8;
+constexpr int kMaxStreamItems = 224;        // a kernel argument of under 4 KB
+constexpr uint64_t kStreamShared = 1ull << 32;
+struct StreamBatch {
+  const uint8_t* w[kMaxStreamItems];
+  uint64_t at[kMaxStreamItems];
+  uint8_t rows[kMaxStreamItems];
+  int32_t n_items;
+};
+bool stream_supported(const FfnShape& s);
+hipError_t launch_stream_gateup(const StreamBatch& b, const FfnShape& s, const void* x, const int32_t* perm, int k,
+                                void* h, hipStream_t st, const LaunchTiming& tm);
+hipError_t launch_stream_down(const StreamBatch& b, const FfnShape& s, const void* h, const int32_t* perm, int k,
+                              void* buf, bool bf16_out, hipStream_t st, const LaunchTiming& tm);
+// The same over the device pager's plan, faulted experts streamed from their masters (as launch_ffn_dev): gate/up, then
+// down into buf.
+hipError_t launch_stream_dev(const FfnBatch* plan, int max_items, const FfnShape& s, const void* x, void* h, float* buf,
+                             hipStream_t st, const LaunchTiming& tm_gateup, const LaunchTiming& tm_down);
+
 // Device-planned FFN of one layer-step (plan written to HBM by the device pager): gate/up, with
 // faulted experts streamed from their pinned masters into their slots by the same kernel, then (if
 // with_down) down into buf for the caller's combine.  max_items bounds the plan (T*k + shared).
