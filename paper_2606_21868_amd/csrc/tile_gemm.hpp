@@ -162,8 +162,15 @@ __device__ __forceinline__ void tile_body(const GroupedBatch& gb, const uint16_t
   const int n_tiles = gb.tile_end[gb.n_groups - 1] * n_ct;
   const int G = static_cast<int>(gridDim.x);
   const int xcd = static_cast<int>(blockIdx.x) % 8, jx = static_cast<int>(blockIdx.x) / 8;
+  // XCD-aware: workgroups are dealt to the 8 XCDs round-robin; in a full round the workgroups of one XCD take
+  // consecutive tiles (the column tiles of a few experts, whose token rows then stay in that XCD's L2).  The
+  // last, partial round is dealt round-robin instead: the tiles left over would all fall to the first XCDs and wait
+  // for their share of the memory system (510 -> 475 us for 2208 tiles over 512
+  // workgroups, 66 -> 55 for 704).
   const int L = xcd * (G / 8) + min(xcd, G % 8) + jx;
-  const int my_tiles = (n_tiles - L + G - 1) / G;
+  const int full = n_tiles / G;
+  const int my_tiles = full + (static_cast<int>(blockIdx.x) < n_tiles - full * G ? 1 : 0);
+  auto tile_no = [&](int i) __attribute__((always_inline)) { return i * G + (i < full ? L : static_cast<int>(blockIdx.x)); };
   const int nq = my_tiles * spt;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int c = lane & 15, g = lane >> 4;
@@ -214,7 +221,7 @@ __device__ __forceinline__ void tile_body(const GroupedBatch& gb, const uint16_t
       for (int j = 0; j < AR; ++j) avo[j] = kOutOfRange;
       return;
     }
-    const T t = decode(L + i * G);
+    const T t = decode(tile_no(i));
     w_rs = rsrc_words(t.w + off0, w_bytes);
     const bool on = t.c0 + wave * CW < cols;
 #pragma unroll
@@ -243,7 +250,7 @@ __device__ __forceinline__ void tile_body(const GroupedBatch& gb, const uint16_t
                    ? static_cast<uint32_t>(rr) * arow + (((lane & 7) ^ swz((wave * RW + rl) & 15)) << 4)
                    : kOutOfRange;
     }
-    if (i + 1 < my_tiles) pn = pair_of(decode(L + (i + 1) * G));
+    if (i + 1 < my_tiles) pn = pair_of(decode(tile_no(i + 1)));
   };
   u32x4_t W[kTB][2][2];
   uint32_t S[kTB][2];
@@ -267,7 +274,7 @@ __device__ __forceinline__ void tile_body(const GroupedBatch& gb, const uint16_t
 
   f32x4_t acc[2][NSL] = {};
   int cs_tile = 0, cs_s = 0;
-  T ct = decode(L);
+  T ct = decode(tile_no(0));
   pn = pair_of(ct);
   __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
   auto epilogue = [&]() __attribute__((always_inline)) {
@@ -384,7 +391,7 @@ __device__ __forceinline__ void tile_body(const GroupedBatch& gb, const uint16_t
 #pragma unroll
         for (int s = 0; s < NSL; ++s) acc[b][s] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       cs_s = 0;
-      if (++cs_tile < my_tiles) ct = decode(L + cs_tile * G);
+      if (++cs_tile < my_tiles) ct = decode(tile_no(cs_tile));
     }
   };
   // the loop is unrolled over the ring, so that slots and register sets have fixed indices.  Each way out

@@ -25,6 +25,8 @@ CASES = {
     "fp8 few rows": (FP8_BATCH.with_(L=2, T=16, d=256, I=256, N=64, k=4), 20),
     # bf16, widths that are multiples of 64 only (a last tile of one wave), with a shared expert
     "bf16 shared": (BF16_BATCH.with_(L=2, T=37, d=320, I=192, N=12, k=3, has_shared=True), 5),
+    # more tiles than workgroups, by a part of a round (704 and 768 tiles over 512 when all experts are resident)
+    "bf16 partial round": (BF16_BATCH.with_(L=1, T=203, d=1472, I=704, N=60, k=6, has_shared=True), 20),
     # bf16, the same widths without one, K of one stage, wide tiles with a last column tile of half a tile
     "bf16 wide": (BF16_BATCH.with_(L=1, T=500, d=320, I=64, N=8, k=2), 3),
 }
