@@ -1567,7 +1567,7 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
         WISP_HIP(launch_stream_dev(ctx->d_plan, max_items, ctx->shape, xl, ctx->h, ctx->buf, sm, t3, t4),
                  "device-planned FFN launch");
       else
-        WISP_HIP(launch_ffn_dev(ctx->d_plan, max_items, ctx->shape, xl, ctx->h, ctx->buf, !dc, sm, t3, t4),
+        WISP_HIP(launch_ffn_dev(ctx->d_plan, max_items, ctx->shape, xl, ctx->h, ctx->buf, !dc, T == 1, sm, t3, t4),
                  "device-planned FFN launch");
       timing_end(ctx, t3, WISP_K_FFN_GATEUP, 0);
       if (!dc) timing_end(ctx, t4, WISP_K_FFN_DOWN, 0);

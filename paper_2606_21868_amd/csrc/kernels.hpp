@@ -106,9 +106,10 @@ hipError_t launch_stream_dev(const FfnBatch* plan, int max_items, const FfnShape
 
 // Device-planned FFN of one layer-step (plan written to HBM by the device pager): gate/up, with
 // faulted experts streamed from their pinned masters into their slots by the same kernel, then (if
-// with_down) down into buf for the caller's combine.  max_items bounds the plan (T*k + shared).
+// with_down) down into buf for the caller's combine.  max_items bounds the plan (T*k + shared); one_token: a step of
+// one token (every item has one).
 hipError_t launch_ffn_dev(const FfnBatch* plan, int max_items, const FfnShape& s, const void* x, void* h,
-                          float* buf, bool with_down, hipStream_t st, const LaunchTiming& tm_gateup,
+                          float* buf, bool with_down, bool one_token, hipStream_t st, const LaunchTiming& tm_gateup,
                           const LaunchTiming& tm_down);
 bool ffn_dev_supported(const FfnShape& s, int T, int k, int has_shared);
 
