@@ -83,6 +83,9 @@ struct LayerState {
   std::vector<int32_t> pf_req;       // ids requested for this layer by the last decode step
 };
 
+// One item of a streamed launch: an expert blob and up to kStreamRows of its rows (StreamBatch).
+struct StreamItem { const uint8_t* w; uint64_t at; int32_t rows; };
+
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
@@ -134,7 +137,11 @@ struct wisp_ctx {
   int32_t perm_layer = -1, perm_T = 0;
   std::vector<int32_t> perm_ids;     // the ids the early permutation was computed from
   std::vector<int32_t> e_cnt, e_off; // pairs per expert and their first sorted row
-  std::vector<int32_t> pair_order;   // pairs sorted by expert (host copy, for the per-item path)
+  std::vector<int32_t> pair_order;   // pairs sorted by expert (host copy, for the per-item and streamed paths)
+  // scratch of a layer-step, kept so that the way from the routed ids to the first launch allocates nothing
+  std::vector<int32_t> fill_scratch; // [N]
+  std::vector<uint8_t> planned;      // [N]
+  std::vector<StreamItem> items[3];  // hits, and each half of the faults
   // routing-blind static offload (comparison arm)
   struct Offload {
     bool on = false;
@@ -581,7 +588,6 @@ uint64_t ffn_bytes(const wisp_ctx* c, const FfnBatch& b, bool gateup) {
 // kMaxItems items; the per-(token, rank) outputs land in buf.
 struct Pair { int32_t t, out; };
 struct Work { const uint8_t* w; std::vector<Pair> pairs; };
-struct StreamItem { const uint8_t* w; uint64_t at; int32_t rows; };   // StreamBatch
 
 // The launches of a list of stream items (launch_stream_*), counted as the given kernel classes.
 wisp_status run_stream(wisp_ctx* c, const std::vector<StreamItem>& items, const void* x, const int32_t* perm,
@@ -1231,9 +1237,11 @@ wisp_status page_in_ids(wisp_ctx* ctx, int32_t layer, const int32_t* ids_host, i
   if ((s = ensure_events(L.fill_ev, 2 * nch)) != WISP_OK) return s;
   if ((s = ensure_events(L.chunk_ev, 2 * nch)) != WISP_OK) return s;
   if (L.late.size() < nch) L.late.resize(nch);
-  L.chunk_ptrs.assign(nch, {});
-  for (size_t ci = 0; ci < nch; ++ci)
+  if (L.chunk_ptrs.size() < nch) L.chunk_ptrs.resize(nch);
+  for (size_t ci = 0; ci < nch; ++ci) {
+    L.chunk_ptrs[ci].clear();
     for (int32_t sl : L.plan.chunks[ci].slots) L.chunk_ptrs[ci].push_back(L.slot_mem[sl]);
+  }
   L.pending = true;
   wisp_page_stats ps{};
   ps.hits = L.plan.hits;
@@ -1299,12 +1307,14 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
   if (L.from_counts && (!grouped || ctx->perm_layer != layer || ctx->perm_T != T))
     return fail(WISP_E_STATE, "a page-in from device counts needs its layer's device permutation");
   if (!grouped) {   // the per-item launches list their pairs; the grouped ones read the device order
-    std::vector<int32_t> fill(off.begin(), off.end() - 1);
+    std::vector<int32_t>& fill = ctx->fill_scratch;
+    fill.assign(off.begin(), off.end() - 1);
     for (int32_t p = 0; p < n_pairs; ++p) ctx->pair_order[fill[L.ids[p]]++] = p;
   }
   // exactness check: every routed id is in a chunk of the plan, with a slot
   {
-    std::vector<uint8_t> planned(N, 0);
+    std::vector<uint8_t>& planned = ctx->planned;
+    planned.assign(N, 0);
     for (size_t ci = 0; ci < nch; ++ci)
       for (int32_t e : L.plan.chunks[ci].experts) planned[e] = 1;
     for (int e = 0; e < N; ++e)
@@ -1402,6 +1412,39 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
         if (!faults[h].empty()) {
           WISP_HIP(hipStreamWaitEvent(sm, L.fill_ev[2 * ci + h], 0), "hipStreamWaitEvent(fill)");
           if ((s = run_grouped(ctx, faults[h], x_dev, T, cnt, off, sm)) != WISP_OK) return s;
+        }
+        if (nch > 1) WISP_HIP(hipEventRecord(L.chunk_ev[2 * ci + h], sm), "hipEventRecord(chunk)");
+      }
+    } else if (stream_tokens(ctx, T)) {
+      // the experts' items straight from the sorted pairs
+      std::vector<StreamItem>* items = ctx->items;
+      for (int h = 0; h < 3; ++h) items[h].clear();
+      for (size_t i = 0; i < cp.experts.size(); ++i) {
+        const int32_t e = cp.experts[i];
+        std::vector<StreamItem>& to = items[cp.fault[i] ? 1 + L.late[ci][i] : 0];
+        for (int32_t q = off[e]; q < off[e + 1]; ++q) {
+          const int32_t p = ctx->pair_order[q], i0 = (q - off[e]) % kStreamRows, t = p / k;
+          if (i0 == 0) to.push_back({L.chunk_ptrs[ci][i], 0, 0});
+          StreamItem& it = to.back();
+          it.at |= static_cast<uint64_t>(t) << (4 * i0) | static_cast<uint64_t>(p - t * k) << (32 + 4 * i0);
+          it.rows = i0 + 1;
+        }
+      }
+      if (ci == 0 && ctx->desc.has_shared)
+        for (int32_t t = 0; t < T; ++t) {
+          if (t % kStreamRows == 0) items[0].push_back({L.shared_dev, 0, 0});
+          StreamItem& it = items[0].back();
+          it.at |= static_cast<uint64_t>(t) << (4 * it.rows) | static_cast<uint64_t>(k) << (32 + 4 * it.rows);
+          ++it.rows;
+        }
+      auto run = [&](const std::vector<StreamItem>& v) {
+        return run_stream(ctx, v, x_dev, nullptr, false, WISP_K_FFN_GATEUP, WISP_K_FFN_DOWN, sm);
+      };
+      if (!items[0].empty() && (s = run(items[0])) != WISP_OK) return s;
+      for (int h = 0; h < 2; ++h) {
+        if (!items[1 + h].empty()) {
+          WISP_HIP(hipStreamWaitEvent(sm, L.fill_ev[2 * ci + h], 0), "hipStreamWaitEvent(fill)");
+          if ((s = run(items[1 + h])) != WISP_OK) return s;
         }
         if (nch > 1) WISP_HIP(hipEventRecord(L.chunk_ev[2 * ci + h], sm), "hipEventRecord(chunk)");
       }

@@ -42,9 +42,9 @@ void SlotTable::import_state(const int32_t* pi, const int32_t* pinv, const uint6
 // tick (all experts of a step share it).
 void SlotTable::alg1(const int32_t* G, int32_t g, ChunkPlan* cp) {
   for (int32_t i = 0; i < g; ++i) mark_[G[i]] = 1;
-  std::vector<int32_t> res, flt;
-  res.reserve(g);
-  flt.reserve(g);
+  std::vector<int32_t>&res = res_, &flt = flt_;
+  res.clear();
+  flt.clear();
   for (int32_t i = 0; i < g; ++i) (pi_[G[i]] >= 0 ? res : flt).push_back(G[i]);
   std::sort(res.begin(), res.end());
   std::sort(flt.begin(), flt.end());
@@ -79,17 +79,16 @@ bool SlotTable::step(const int32_t* ids, int32_t n, StepPlan* plan) {
   for (int32_t i = 0; i < n; ++i)
     if (ids[i] < 0 || ids[i] >= N_) return false;
   // distinct ids
-  std::vector<int32_t> R;
-  R.reserve(n);
+  std::vector<int32_t>& R = distinct_;
+  R.clear();
   for (int32_t i = 0; i < n; ++i)
     if (!mark_[ids[i]]) { mark_[ids[i]] = 1; R.push_back(ids[i]); }
   for (int32_t e : R) mark_[e] = 0;
-  plan->chunks.clear();
   plan->hits = plan->misses = 0;
   const int32_t nr = static_cast<int32_t>(R.size());
+  plan->chunks.resize(nr == 0 ? 0 : 1);   // (the usual single chunk keeps its vectors from step to step)
   if (nr == 0) return true;
   if (nr <= C_) {
-    plan->chunks.emplace_back();
     alg1(R.data(), nr, &plan->chunks.back());
   } else {
     // residency is judged once, at the start of the layer-step
@@ -99,6 +98,7 @@ bool SlotTable::step(const int32_t* ids, int32_t n, StepPlan* plan) {
     std::sort(non.begin(), non.end());
     std::vector<int32_t> ord(res);
     ord.insert(ord.end(), non.begin(), non.end());
+    plan->chunks.clear();
     for (int32_t off = 0; off < nr; off += C_) {
       plan->chunks.emplace_back();
       alg1(ord.data() + off, std::min(C_, nr - off), &plan->chunks.back());

@@ -63,7 +63,7 @@ class SlotTable {
   uint64_t clock_ = 0;
   // scratch
   std::vector<uint8_t> mark_;
-  std::vector<int32_t> cand_;
+  std::vector<int32_t> cand_, res_, flt_, distinct_;
 };
 
 }  // namespace wisp
