@@ -18,10 +18,11 @@
 // Every output is one fixed chain over K, whatever tile, row block or launch holds its row, so paged and
 // resident runs give the same bits.
 //
-// Measured (64 fp8 experts + shared, d 7168, I 2048, 301 tokens): gate/up 510 us, down 252 us, against 5.30
-// and 3.26 ms of the per-item kernels.  With work taken out (scratch copies): no MFMAs and LDS reads
-// 447 / 233 us, no token rows 464 / 237, the weight stream alone 396 / 219 (4.8 TB/s; strided rows stream
-// at 5.1-5.7 TB/s here, a plain read at 7.0).
+// Measured (64 fp8 experts + shared, d 7168, I 2048, 301 tokens): gate/up 461 us, down 254 us, against 5.30
+// and 3.26 ms of the per-item kernels.  With work taken out (scratch copies of an earlier 510 / 252 us build): no
+// MFMAs and LDS reads 447 / 233 us, no token rows 464 / 237, the weight stream alone 396 / 219 (4.8 TB/s;
+// 369 us of gate/up's 475 once the last round of tiles was dealt over the XCDs).  Strided rows stream
+// at 5.1-5.7 TB/s here, a plain read at 7.0.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -71,22 +72,40 @@ __device__ __forceinline__ void lds_write_i32(uint32_t addr, int32_t v) {
 }
 __device__ __forceinline__ u32x4_t lds_read_4(uint32_t addr) {
   u32x4_t v;
-  asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(addr) : "memory");
+  asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)\n\t; pin %0" : "=&v"(v) : "v"(addr) : "memory");
   return v;
 }
-// four fragments: a0, a1 and the same DELTA bytes further, read by inline ds_reads (the compiler would
-// make plain LDS reads wait for every buffer-to-LDS load in flight)
+// Four fragments of a batch of slabs: a0, a1 and the same DELTA bytes further, read by inline ds_reads (the compiler
+// would make plain LDS reads wait for every buffer-to-LDS load in flight).  A batch's reads go out before the
+// batch ahead of it is used: read_next issues them and waits for the batch before (LDS reads return in order),
+// whose registers the compiler reads only after that; read_last waits for the last.  One wait per batch for its
+// own reads took 733 us per fp8 layer pass where this takes 720 (301 tokens, the shape above), 1828 against 1670 (1100).
 template <int DELTA>
-__device__ __forceinline__ void read_frags4(u32x4_t (&f)[4], uint32_t a0, uint32_t a1) {
+__device__ __forceinline__ void read_first(u32x4_t (&f)[4], uint32_t a0, uint32_t a1) {
   asm volatile(
       "ds_read_b128 %0, %4\n\t"
       "ds_read_b128 %1, %5\n\t"
       "ds_read_b128 %2, %4 offset:%6\n\t"
-      "ds_read_b128 %3, %5 offset:%6\n\t"
-      "s_waitcnt lgkmcnt(0)"
+      "ds_read_b128 %3, %5 offset:%6"
       : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3])
       : "v"(a0), "v"(a1), "i"(DELTA)
       : "memory");
+}
+template <int DELTA>
+__device__ __forceinline__ void read_next(u32x4_t (&f)[4], u32x4_t (&n)[4], uint32_t a0, uint32_t a1) {
+  asm volatile(
+      "ds_read_b128 %4, %8\n\t"
+      "ds_read_b128 %5, %9\n\t"
+      "ds_read_b128 %6, %8 offset:%10\n\t"
+      "ds_read_b128 %7, %9 offset:%10\n\t"
+      "s_waitcnt lgkmcnt(4)\n\t"
+      "; pin %0 %1 %2 %3"
+      : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "=&v"(n[0]), "=&v"(n[1]), "=&v"(n[2]), "=&v"(n[3])
+      : "v"(a0), "v"(a1), "i"(DELTA)
+      : "memory");
+}
+__device__ __forceinline__ void read_last(u32x4_t (&f)[4]) {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\t; pin %0 %1 %2 %3" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : : "memory");
 }
 // 16 E4M3 codes to bf16 (exact): the first and the last eight
 __device__ __forceinline__ void fp8_to_bf16(u32x4_t v, bf16x8_t& lo, bf16x8_t& hi) {
@@ -354,12 +373,20 @@ __device__ __forceinline__ void tile_body(const GroupedBatch& gb, const uint16_t
           sc[b] = __uint_as_float(S[U][b] << 16);
         }
       }
+      // bf16: steps 0, 1 of slabs sl, sl + 1; fp8: steps 0 .. 3 of slab sl
+      constexpr int DELTA = WT == DT_BF16 ? 2048 : RB * 128;
+      u32x4_t fr[2][4];
+      read_first<DELTA>(fr[0], fo[0] + U * ASLOT, fo[1] + U * ASLOT);
 #pragma unroll
       for (int sl = 0; sl < NSL; sl += SB) {
+        // read also for slabs past the last row (within the slot, and not used): a branch around the reads
+        // would make the compiler copy registers that are still in flight
+        u32x4_t(&f)[4] = fr[(sl / SB) & 1];
+        if (sl + SB < NSL)
+          read_next<DELTA>(f, fr[(sl / SB + 1) & 1], fo[0] + U * ASLOT + (sl + SB) * 2048, fo[1] + U * ASLOT + (sl + SB) * 2048);
+        else
+          read_last(f);
         if (sl < ns) {
-          u32x4_t f[4];
-          // bf16: steps 0, 1 of slabs sl, sl + 1; fp8: steps 0 .. 3 of slab sl
-          read_frags4<WT == DT_BF16 ? 2048 : RB * 128>(f, fo[0] + U * ASLOT + sl * 2048, fo[1] + U * ASLOT + sl * 2048);
           if constexpr (WT == DT_BF16) {
 #pragma unroll
             for (int s = 0; s < 2; ++s)

@@ -1,6 +1,7 @@
 """Build-time guard of the any-width grouped GEMMs: their weights are loaded into registers by inline asm that the
-compiler does not track and read only after an explicit wait, so the kernels must neither spill nor use
-scratch, and no instruction may touch such a register between its load and the marker after the wait."""
+compiler does not track and read only after an explicit wait (and so are the token fragments, from LDS), so the
+kernels must neither spill nor use scratch, and no instruction may touch such a register between its load and the
+marker after the wait."""
 import os
 import re
 import shutil
@@ -39,7 +40,7 @@ def test_tile_kernels_keep_their_registers(tmp_path):
                 continue
             if not s or s[0] in ";.":
                 continue
-            m = re.match(r"(buffer_load_dwordx4|buffer_load_ushort) (v\[\d+:\d+\]|v\d+), ", s)
+            m = re.match(r"(buffer_load_dwordx4|buffer_load_ushort|ds_read_b128) (v\[\d+:\d+\]|v\d+), ", s)
             if m and not s.endswith("lds"):
                 loads += 1
                 assert not _regs(s[m.end():]) & in_flight, (name, s)
