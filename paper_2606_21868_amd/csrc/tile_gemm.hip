@@ -38,19 +38,20 @@ hipError_t launch(GroupedBatch b, const FfnShape& s, const void* a, uint32_t a_b
   return hipGetLastError();
 }
 
-// Few rows per expert: two four-wave workgroups per CU with tiles of 64 h (128 output) columns, which split
-// the launch finer; from a mean of 48 rows one eight-wave workgroup with row blocks of 128, which reads an
-// expert's weights once more rarely and its token rows half as often.  us per layer pass at mean rows
-// 38 / 64 (fp8, d 7168): 814 against 881, 1112 against 1011; at 40 / 102 (bf16, d 1472): 251 against 252, 307 against 282.
-// The choice does not change a bit of any output.
+// Row blocks of 64 in two four-wave workgroups per CU, with tiles of 64 h (128 output) columns, which split the
+// launch finer; or row blocks of 128 in one eight-wave workgroup, which reads an expert's weights for more
+// rows at once and its token rows half as often.  The second is the better one once it saves a quarter of the row
+// blocks, that is when a part of the experts has more than 64 rows.  us per layer pass at mean rows 38 / 50 /
+// 57 / 64 / 87 (64 fp8 experts, d 7168): 740 against 870, 817 against 920, 876 against 935, 1005 against 953,
+// 1304 against 1009; at 20 / 52 / 62 / 80 / 150 (60 bf16 experts, d 1472): 254 against 290, 314 against 325, 336
+// against 325, 392 against 339, 544 against 476.  The choice does not change a bit of any output.
 bool wide_rows(const GroupedBatch& b) {
-  int64_t rows = 0, n = 0;
-  for (int g = 0; g < b.n_groups; ++g)
-    if (g != b.shared) {
-      rows += b.rows[g];
-      ++n;
-    }
-  return n == 0 ? b.rows[0] > 64 : rows > 48 * n;
+  int64_t n64 = 0, n128 = 0;
+  for (int g = 0; g < b.n_groups; ++g) {
+    n64 += (b.rows[g] + 63) / 64;
+    n128 += (b.rows[g] + 127) / 128;
+  }
+  return 3 * n64 > 4 * n128;
 }
 
 template <int MODE>
