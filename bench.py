@@ -701,7 +701,8 @@ def main():
     pageable_masters = wl.L * wl.N * wl.blob > PINNED_LIMIT_BYTES
     if pageable_masters:
         args.pager = "host"
-    run = wisp.DecodeRun(wl, device=0, steps=total, pageable=pageable_masters)
+    # inputs for the workload's own length at least: the side legs run a fixed number of steps, whatever is timed
+    run = wisp.DecodeRun(wl, device=0, steps=max(total, wl.steps), pageable=pageable_masters)
     t0 = time.time()
     run.generate()
     log(f"generated {wl.L * wl.N} expert blobs ({wl.L * wl.N * wl.blob / 1e9:.1f} GB "
