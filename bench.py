@@ -58,7 +58,7 @@ TRAFFIC_SUMMARIES = {
     ("deepseek-v3-16l-decode", "ffn_gateup"): os.path.join(ROOT, "profiles",
                                                            "ffn_gateup_fp8_deepseek-v3-16l-decode_profile.txt"),
 }
-FFN_SOURCE = os.path.join(ROOT, "paper_2606_21868_amd", "csrc", "expert_ffn.hip")
+CSRC = os.path.join(ROOT, "paper_2606_21868_amd", "csrc")
 
 
 def log(msg):
@@ -97,10 +97,12 @@ def measured_traffic(workload, kname):
         parts = line.split()
         if len(parts) >= 2 and parts[0].startswith("traffic_"):
             fields[parts[0]] = float(parts[1])
-        elif parts[:2] == ["kernel_source", "expert_ffn.hip"] and len(parts) == 4:
-            fields["sha256"] = parts[3]
-    with open(FFN_SOURCE, "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != fields.get("sha256"):
+        elif parts[:1] == ["kernel_source"] and len(parts) == 4:
+            fields["source"], fields["sha256"] = os.path.join(CSRC, os.path.basename(parts[1])), parts[3]
+    if not os.path.exists(fields.get("source", "")):
+        return None
+    with open(fields["source"], "rb") as f:
+        if hashlib.sha256(f.read()).hexdigest() != fields["sha256"]:
             return None
     if "traffic_bytes_per_launch" not in fields:
         return None
