@@ -98,8 +98,9 @@ __device__ __forceinline__ void stream_rows(const uint8_t* w, uint8_t* wr, const
   __shared__ float part[2][4][KW > 1 ? V : 1];    // KW > 1: the waves' sums of one token
   const int K = MODE == MODE_UP ? d : I;
   const int chunks = K * WB / 16;
-  // a chunk past the row's end (where the lanes do not divide the row) repeats the row's last chunk and meets
-  // zeros
+  // a chunk past the row's end (where the lanes do not divide the row) repeats the row's last chunk; its inputs and its
+  // weights (fp8, whose codes are finite: its scale) are then replaced by zeros, both, as an infinite weight times a zero
+  // input is no number
   const int c0 = (wave % KW) * (NL * LPR) + sl;
   int ci[NL];
 #pragma unroll
@@ -149,6 +150,15 @@ __device__ __forceinline__ void stream_rows(const uint8_t* w, uint8_t* wr, const
       }
     }
     if (chunks != KW * NL * LPR) {
+      if (!FP8 && i == 0) {   // once, with the first row's inputs on their way too
+#pragma unroll
+        for (int m = KW > 1 ? 0 : NL - 1; m < NL; ++m)
+#pragma unroll
+          for (int q = 0; q < NM; ++q)
+#pragma unroll
+            for (int p = 0; p < RP; ++p)
+              if (c0 + m * LPR >= chunks) wv[q][p][m] = u32x4_t{0u, 0u, 0u, 0u};
+      }
 #pragma unroll
       for (int m = KW > 1 ? 0 : NL - 1; m < NL; ++m)
 #pragma unroll
@@ -167,6 +177,7 @@ __device__ __forceinline__ void stream_rows(const uint8_t* w, uint8_t* wr, const
             // would), they take twice the registers and a wave per SIMD (57 us a launch instead of 43)
             asm volatile("" : "+v"(wv[q][p][m]));
             s = __uint_as_float(static_cast<uint32_t>(__shfl(static_cast<int>(sv[q][p]), m * (LPR / 8) + sl / 8, LPR)) << 16);
+            if ((KW > 1 || m == NL - 1) && c0 + m * LPR >= chunks) s = 0.f;
           }
           v[q * RP + p] = chunk_dot<WT>(wv[q][p][m], x[m], s, v[q * RP + p]);
         }
