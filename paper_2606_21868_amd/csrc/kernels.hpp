@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "router_rules.hpp"
+
 namespace wisp {
 
 // Element formats (same codes as wisp_dtype).
@@ -163,7 +165,6 @@ int compute_units();   // of the current device
 // Router: logits[t, e] = W_r[e] . x[t] (fp32 accumulate), written as *n_split partial sums over column
 // slices (slice s at logits + s * T * N; 1 for decode sizes, at most kRouterMaxSplit), which the
 // selection adds in slice order.  logits must hold kRouterMaxSplit * T * N floats.
-constexpr int kRouterMaxSplit = 8;
 hipError_t launch_router_logits(const float* wr, const void* x, int x_dtype, int T, int N, int d, float* logits,
                                 int* n_split, hipStream_t st, const LaunchTiming& tm);
 // Router selection: idx/w [T, k] by routing variant.  If idx_host is given, entry t*k+j of it (in

@@ -13,6 +13,7 @@
 
 #include "kernels.hpp"
 #include "router_row.hpp"
+#include "router_rules.hpp"
 #include "select.hpp"
 
 namespace wisp {
@@ -232,40 +233,25 @@ hipError_t launch_router_logits(const float* wr, const void* x, int x_dtype, int
     return hipGetLastError();
   }
   if (N > 256 || d % 16 != 0) return hipErrorInvalidValue;
-  // Column slices: at most kRouterMaxSplit (the size of the partial sums), of at least four steps, while
-  // 64-token blocks of them fit the chip at once.  Token blocks of
-  // 64 against all rows while they and the slices give every CU a workgroup (the router matrix is then read
-  // once per 64 tokens); below that, blocks of 32 or 16 tokens and groups of 64 rows: a wave's chain of
-  // fp32 matrix-core instructions is then the time (64 x 128 x 256 columns take 6.8 us on one SIMD), and
-  // the chip is empty.37 tokens, 128 experts, d 2048: 12.9 -> 5.4 us; 301 tokens,
-  // 64 experts, d 7168: 33 -> 14.4; 203 tokens, 60 experts, d 1472: 101 (LDS-tiled FMA kernel) -> 5.5.
-  const int total = d / 16;
-  auto blocks = [&](int tb) { return (T + 16 * tb - 1) / (16 * tb); };
-  int S = 1;
-  while (2 * S <= kRouterMaxSplit && total / (2 * S) >= 4 && 2 * S * blocks(4) <= 256) S *= 2;
-  const int steps = (total + S - 1) / S;
-  S = (total + steps - 1) / steps;
-  *n_split = S;
-  const int nb = (N + 15) / 16;
+  // how the logits are cut (router_tiles); 37 tokens, 128 experts, d 2048: 12.9 -> 5.4 us; 301 tokens, 64 experts, d 7168:
+  // 33 -> 14.4; 203 tokens, 60 experts, d 1472: 101 (LDS-tiled FMA kernel) -> 5.5
+  const RouterTiles r = router_tiles(T, N, d);
+  *n_split = r.slices;
   using K = void (*)(const float*, const void*, int, int, int, int, float*);
   K kern = nullptr;
-  int tb = 4, groups = 1;
   const bool f32 = x_dtype == DT_F32;
-  if (blocks(4) * S >= 256) {
-    const int rb = (nb + 3) / 4;
-#define WISP_RK(R) kern = f32 ? &router_logits_split_kernel<DT_F32, R, 4, 4> : &router_logits_split_kernel<DT_BF16, R, 4, 4>
-    if (rb == 1) WISP_RK(1); else if (rb == 2) WISP_RK(2); else if (rb == 3) WISP_RK(3); else WISP_RK(4);
-#undef WISP_RK
+#define WISP_RK(R, TB, PF) \
+  kern = f32 ? &router_logits_split_kernel<DT_F32, R, TB, PF> : &router_logits_split_kernel<DT_BF16, R, TB, PF>
+  if (r.tb == 4) {
+    if (r.rb == 1) WISP_RK(1, 4, 4); else if (r.rb == 2) WISP_RK(2, 4, 4); else if (r.rb == 3) WISP_RK(3, 4, 4); else WISP_RK(4, 4, 4);
+  } else if (r.tb == 2) {
+    WISP_RK(1, 2, 8);
   } else {
-    groups = (nb + 3) / 4;
-    tb = blocks(2) * S * groups >= 256 ? 2 : 1;
-    if (tb == 2)
-      kern = f32 ? &router_logits_split_kernel<DT_F32, 1, 2, 8> : &router_logits_split_kernel<DT_BF16, 1, 2, 8>;
-    else
-      kern = f32 ? &router_logits_split_kernel<DT_F32, 1, 1, 8> : &router_logits_split_kernel<DT_BF16, 1, 1, 8>;
+    WISP_RK(1, 1, 8);
   }
-  hipExtLaunchKernelGGL(kern, dim3(blocks(tb), S, groups), dim3(256), 0, st, tm.start, tm.stop, 0, wr, x, T, N, d, steps,
-                        logits);
+#undef WISP_RK
+  hipExtLaunchKernelGGL(kern, dim3((T + 16 * r.tb - 1) / (16 * r.tb), r.slices, r.groups), dim3(256), 0, st, tm.start,
+                        tm.stop, 0, wr, x, T, N, d, r.steps, logits);
   return hipGetLastError();
 }
 

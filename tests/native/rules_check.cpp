@@ -1,0 +1,19 @@
+// Prints what the launch rules choose for the argument list (router T N d: slices steps token-blocks groups row-blocks).
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "router_rules.hpp"
+
+int main(int argc, char** argv) {
+  for (int i = 1; i < argc;) {
+    if (!std::strcmp(argv[i], "router") && i + 3 < argc) {
+      const wisp::RouterTiles r = wisp::router_tiles(std::atoi(argv[i + 1]), std::atoi(argv[i + 2]), std::atoi(argv[i + 3]));
+      std::printf("%d %d %d %d %d\n", r.slices, r.steps, r.tb, r.groups, r.rb);
+      i += 4;
+    } else {
+      return 2;
+    }
+  }
+  return 0;
+}

@@ -16,7 +16,8 @@ BASE = WORKLOADS["qwen3-30b-a3b-prefill"].with_(L=1, I=64, k=2)
 
 
 @pytest.mark.parametrize("T,N,d,x32", [(5, 24, 256, False), (8, 2, 256, False), (8, 24, 1088, True), (9, 60, 1472, False),
-                                       (17, 3, 320, False), (33, 130, 704, True), (1040, 72, 640, False)])
+                                       (17, 3, 320, False), (33, 130, 704, True), (1040, 72, 640, False),
+                                       (1100, 130, 704, False), (1000, 250, 704, True)])
 def test_routing_against_oracle(T, N, d, x32):
     wl = BASE.with_(T=T, N=N, d=d, **(dict(w_dtype=F32, x_dtype=F32) if x32 else {}))
     log(f"[case] routing T={T} N={N} d={d} {'f32' if x32 else 'bf16'}")

@@ -1,0 +1,47 @@
+"""The lines between the launch forms, on the CPU: the rules are host code of their own headers, built with g++ and asked for
+the sizes on both sides of each line, as timed on the card (figures beside the rules), and for what every form must cover."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_2606_21868_amd", "csrc")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rules") / "rules_check")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-I", CSRC, os.path.join(HERE, "native", "rules_check.cpp"), "-o", exe],
+                   check=True, timeout=120)
+
+    def run(questions):
+        args = [str(a) for q in questions for a in q]
+        r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0
+        return [tuple(int(v) for v in line.split()) for line in r.stdout.splitlines()]
+    return run
+
+
+# tokens, experts, d_model, and whether small workgroups are the faster form there
+@pytest.mark.parametrize("T,N,d,fine", [
+    (9, 256, 7168, True), (700, 256, 7168, True), (800, 256, 7168, False), (1024, 256, 7168, False),
+    (1040, 256, 7168, False), (1984, 256, 7168, False), (2500, 256, 7168, False),
+    (600, 192, 4096, True), (700, 192, 4096, False), (1900, 192, 4096, False),
+    (37, 128, 2048, True), (1024, 128, 2048, True), (1040, 128, 2048, False), (1900, 128, 2048, False), (2048, 128, 2048, False),
+    (301, 64, 7168, True), (1024, 64, 7168, True), (1040, 64, 7168, False), (2500, 64, 7168, False), (203, 60, 1472, True)])
+def test_router_form(ask, T, N, d, fine):
+    slices, steps, tb, groups, rb = ask([("router", T, N, d)])[0]
+    assert (tb < 4) == fine
+
+
+def test_router_forms_cover_every_row_and_column(ask):
+    q = [("router", T, N, d) for T in (9, 16, 17, 64, 65, 500, 1024, 1025, 2048, 2049, 5000) for N in (1, 16, 60, 64, 65, 130, 192, 256)
+         for d in (16, 64, 320, 1472, 2048, 7168)]
+    for (_, T, N, d), (slices, steps, tb, groups, rb) in zip(q, ask(q)):
+        assert 1 <= slices <= 8 and (slices - 1) * steps < d // 16 <= slices * steps
+        assert tb in (1, 2, 4) and groups * rb * 64 >= N > (groups * rb - 1) * 64
+        assert (rb == 1 and groups >= 1) if tb < 4 else groups == 1
