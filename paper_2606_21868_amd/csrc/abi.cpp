@@ -495,12 +495,9 @@ wisp_status poison_slots(wisp_ctx* c, int32_t layer, const std::vector<std::pair
   return WISP_OK;
 }
 
-// Few tokens, whose FFN streams every expert once (stream_gemm.hip), with either pager: fp8 weights, and bf16 from two
-// tokens (one token has the single-token kernels).  us per launch, gate/up + down, against the per-item
-// kernels: fp8, one token (9 experts, d 7168) 42.7 + 24.1 against 57.4 + 36.7; bf16, seven tokens (50 experts, d 2048)
-// 46.9 + 24.7 against 59 + 33; four tokens (6 experts, d 4096) 174 + 92 against 211 + 133.
+// Few tokens, whose FFN streams every expert once (stream_gemm.hip), with either pager.
 bool stream_tokens(const wisp_ctx* c, int32_t T) {
-  return T >= (c->desc.w_dtype == WISP_FP8E4M3_B128 ? 1 : 2) && T <= kStreamMaxTokens && stream_supported(c->shape);
+  return stream_supported(c->shape) && stream_few_tokens(c->blob.d, c->blob.I, static_cast<int>(c->blob.elem), T);
 }
 
 // Token batches with few rows per expert, streamed the same way from the device pair order instead of as grouped

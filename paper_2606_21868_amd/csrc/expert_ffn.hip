@@ -689,7 +689,7 @@ RowsKernel pick_kernel(int lpr, int nl) {
   } else if constexpr (WT == DT_BF16) {
     WISP_K(64, 4) WISP_K(64, 8) WISP_K(32, 3) WISP_K(64, 28) WISP_K(32, 1) WISP_K(16, 1) WISP_K(16, 3)
   } else {
-    // (fp8 rows of few tokens are streamed, stream_gemm.hip)
+    WISP_K(64, 7) WISP_K(64, 2) WISP_K(16, 1)
   }
   // any other shape: runtime chunk count
   WISP_K(64, 0) WISP_K(32, 0) WISP_K(16, 0) WISP_K(8, 0)
@@ -888,10 +888,13 @@ hipError_t launch_ffn_dev(const FfnBatch* plan, int max_items, const FfnShape& s
   WISP_G(DT_BF16, DT_BF16, 64, 4)   // d = 2048
   WISP_G(DT_BF16, DT_BF16, 32, 1)   // d = 256
   WISP_G(DT_BF16, DT_BF16, 16, 3)   // d = 384
+  WISP_G(DT_FP8, DT_BF16, 16, 1)    // d = 256 (fp8 rows of d = 7168 are streamed)
   WISP_G(DT_F32, DT_F32, 64, 1)     // d = 256
   WISP_DD(DT_BF16, DT_BF16, 32, 3)  // I = 768
   WISP_DD(DT_BF16, DT_BF16, 16, 1)  // I = 128
   WISP_DD(DT_BF16, DT_BF16, 8, 3)   // I = 192
+  WISP_DD(DT_FP8, DT_BF16, 64, 2)   // I = 2048
+  WISP_DD(DT_FP8, DT_BF16, 16, 1)   // I = 256
   WISP_DD(DT_F32, DT_F32, 64, 2)    // I = 512
 #undef WISP_G
 #undef WISP_DD

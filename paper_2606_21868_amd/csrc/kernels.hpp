@@ -7,6 +7,7 @@
 #include <cstdint>
 
 #include "router_rules.hpp"
+#include "stream_rules.hpp"
 
 namespace wisp {
 
@@ -86,7 +87,6 @@ hipError_t launch_down_combine_dev(const FfnBatch* plan, int max_items, const Ff
 // perm, packed in at (token of row i at bits 4 i, rank at bits 32 + 4 i: up to kStreamMaxTokens tokens); with
 // perm (the sorted pair order), perm[at .. at + rows), or, with kStreamShared, tokens at .. at + rows of the shared
 // expert.  h and buf rows are token * (k + 1) + rank, as for the per-item kernels; buf in fp32, or bf16 with bf16_out.
-constexpr int kStreamMaxTokens = 15;
 constexpr int kStreamRows = 8;
 constexpr int kMaxStreamItems = 224;        // a kernel argument of under 4 KB
 constexpr uint64_t kStreamShared = 1ull << 32;

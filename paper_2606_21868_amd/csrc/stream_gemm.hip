@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include "blob_copy.hpp"
+#include "stream_rules.hpp"
 #include "tile_gemm.hpp"
 
 namespace wisp {
@@ -273,23 +274,7 @@ __global__ void __launch_bounds__(256) stream_down_dev(const FfnBatch* __restric
                                                   soff0, 0, buf);
 }
 
-struct Shape { int lpr, nl, kw; };
-
-// lanes, chunks per lane and waves per row with the least padding (whole lines of a row per load)
-constexpr Shape kShapes[] = {{64, 1, 1}, {64, 2, 1}, {64, 3, 1}, {64, 4, 1}, {64, 5, 1}, {64, 6, 1}, {64, 7, 1},
-                             {64, 8, 1}, {32, 1, 1}, {32, 3, 1}, {32, 5, 1}, {16, 1, 1}, {16, 3, 1}, {64, 3, 4},
-                             {64, 4, 4}, {64, 5, 4}, {64, 6, 4}, {64, 7, 4}, {64, 8, 4}};
-bool pick(int chunks, Shape* o) {
-  int best = 0;
-  for (const Shape& s : kShapes) {
-    const int pad = s.lpr * s.nl * s.kw;
-    if (pad >= chunks && (s.kw == 1 || chunks > 512) && (!best || pad < best)) {
-      best = pad;
-      *o = s;
-    }
-  }
-  return best > 0 && 4 * best <= 5 * chunks;   // at most a quarter read for nothing
-}
+using Shape = StreamLanes;
 
 using Kern = void (*)(const StreamBatch, const uint8_t*, const int32_t*, int, int, int, uint32_t, uint32_t, uint32_t,
                       uint32_t, int, void*);
@@ -307,7 +292,7 @@ using DevUp = void (*)(const FfnBatch*, const uint8_t*, int, int, int, int, uint
                        uint32_t, uint32_t, uint16_t*);
 using DevDn = void (*)(const FfnBatch*, const uint8_t*, int, int, uint32_t, uint32_t, float*);
 
-// the shapes of the device pager (ffn_dev_supported)
+// the shapes of the device pager (ffn_dev_supported) that stream (stream_few_tokens)
 template <int WT>
 DevUp dev_up_of(const Shape& s, int* rows_per_wg) {
 #define WISP_U(L, N)                                                                 \
@@ -316,9 +301,9 @@ DevUp dev_up_of(const Shape& s, int* rows_per_wg) {
     return &stream_gateup_dev<WT, L, N, row_slots<MODE_UP, L, N, 1>()>;              \
   }
   if constexpr (WT == DT_BF16) {
-    WISP_U(64, 4) WISP_U(32, 1) WISP_U(16, 3)   // d = 2048, 256, 384
+    WISP_U(64, 4)                  // d = 2048
   } else {
-    WISP_U(64, 7) WISP_U(16, 1)                 // d = 7168, 256
+    WISP_U(64, 7)                  // d = 7168
   }
 #undef WISP_U
   return nullptr;
@@ -331,9 +316,9 @@ DevDn dev_dn_of(const Shape& s, int* rows_per_wg) {
     return &stream_down_dev<WT, L, N, row_slots<MODE_DN, L, N, 1>()>;                \
   }
   if constexpr (WT == DT_BF16) {
-    WISP_D(32, 3) WISP_D(16, 1)                 // I = 768, 128
+    WISP_D(32, 3)                  // I = 768
   } else {
-    WISP_D(64, 2) WISP_D(16, 1)                 // I = 2048, 256
+    WISP_D(64, 2) WISP_D(16, 1)    // I = 2048, 256
   }
 #undef WISP_D
   return nullptr;
@@ -363,7 +348,7 @@ hipError_t launch(const StreamBatch& b, const FfnShape& s, const void* vin, cons
   constexpr bool up = MODE == MODE_UP;
   const BlobLayout& B = s.blob;
   Shape sh{};
-  if (!pick((up ? B.d : B.I) * static_cast<int>(B.elem) / 16, &sh)) return hipErrorInvalidValue;
+  if (!stream_lanes((up ? B.d : B.I) * static_cast<int>(B.elem) / 16, &sh)) return hipErrorInvalidValue;
   int rpw = 0;
   Kern kern = B.w_dtype == DT_FP8 ? kernel_of<DT_FP8, MODE>(sh, &rpw) : kernel_of<DT_BF16, MODE>(sh, &rpw);
   if (!kern) return hipErrorInvalidValue;
@@ -376,7 +361,7 @@ hipError_t launch(const StreamBatch& b, const FfnShape& s, const void* vin, cons
 
 Shape shape_of(const BlobLayout& B, bool up) {
   Shape sh{};
-  (void)pick((up ? B.d : B.I) * static_cast<int>(B.elem) / 16, &sh);
+  (void)stream_lanes((up ? B.d : B.I) * static_cast<int>(B.elem) / 16, &sh);
   return sh;
 }
 
@@ -409,10 +394,8 @@ hipError_t launch_stream_dev(const FfnBatch* plan, int max_items, const FfnShape
 }
 
 bool stream_supported(const FfnShape& s) {
-  Shape sh{};
-  const int e = static_cast<int>(s.blob.elem);
-  return s.x_dtype == DT_BF16 && s.h_dtype == DT_BF16 && s.blob.bytes < (1ull << 32) && pick(s.blob.d * e / 16, &sh) &&
-         pick(s.blob.I * e / 16, &sh);
+  return s.x_dtype == DT_BF16 && s.h_dtype == DT_BF16 && s.blob.bytes < (1ull << 32) &&
+         stream_widths(s.blob.d, s.blob.I, static_cast<int>(s.blob.elem));
 }
 
 hipError_t launch_stream_gateup(const StreamBatch& b, const FfnShape& s, const void* x, const int32_t* perm, int k,

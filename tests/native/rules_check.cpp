@@ -1,9 +1,11 @@
-// Prints what the launch rules choose for the argument list (router T N d: slices steps token-blocks groups row-blocks).
+// Prints what the launch rules choose for the argument list: router T N d (slices steps token-blocks groups row-blocks),
+// few d I elem T (1 if up to 15 tokens stream their experts).
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 
 #include "router_rules.hpp"
+#include "stream_rules.hpp"
 
 int main(int argc, char** argv) {
   for (int i = 1; i < argc;) {
@@ -11,6 +13,9 @@ int main(int argc, char** argv) {
       const wisp::RouterTiles r = wisp::router_tiles(std::atoi(argv[i + 1]), std::atoi(argv[i + 2]), std::atoi(argv[i + 3]));
       std::printf("%d %d %d %d %d\n", r.slices, r.steps, r.tb, r.groups, r.rb);
       i += 4;
+    } else if (!std::strcmp(argv[i], "few") && i + 4 < argc) {
+      std::printf("%d\n", wisp::stream_few_tokens(std::atoi(argv[i + 1]), std::atoi(argv[i + 2]), std::atoi(argv[i + 3]), std::atoi(argv[i + 4])));
+      i += 5;
     } else {
       return 2;
     }

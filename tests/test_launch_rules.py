@@ -45,3 +45,16 @@ def test_router_forms_cover_every_row_and_column(ask):
         assert 1 <= slices <= 8 and (slices - 1) * steps < d // 16 <= slices * steps
         assert tb in (1, 2, 4) and groups * rb * 64 >= N > (groups * rb - 1) * 64
         assert (rb == 1 and groups >= 1) if tb < 4 else groups == 1
+
+
+# widths, bytes of a weight, tokens, and whether streaming whole rows is the faster form there
+@pytest.mark.parametrize("d,I,elem,T,stream", [
+    (2048, 768, 2, 1, False), (2048, 768, 2, 2, True), (2048, 768, 2, 15, True), (2048, 768, 2, 16, False), (7168, 2048, 1, 1, True),
+    (4096, 14336, 2, 4, True), (5120, 8192, 2, 4, True), (1472, 704, 2, 8, True), (1024, 1536, 2, 8, True), (1536, 768, 2, 8, True),
+    (256, 128, 2, 8, False), (512, 512, 2, 8, False), (512, 4096, 2, 8, False), (1024, 1024, 2, 8, False), (960, 960, 2, 8, False),
+    (768, 1024, 2, 8, False), (2048, 256, 2, 8, False), (128, 320, 2, 8, False), (384, 768, 2, 3, False), (320, 192, 2, 8, False),
+    (2048, 768, 1, 2, True), (2944, 768, 1, 1, True), (7168, 256, 1, 1, True), (4096, 512, 1, 1, True),
+    (256, 256, 1, 2, False), (256, 2048, 1, 4, False), (512, 512, 1, 1, False), (1024, 1024, 1, 8, False), (2048, 512, 1, 4, False),
+    (7168, 384, 1, 4, False)])
+def test_few_tokens_form(ask, d, I, elem, T, stream):
+    assert ask([("few", d, I, elem, T)])[0] == (int(stream),)
