@@ -500,14 +500,20 @@ bool stream_tokens(const wisp_ctx* c, int32_t T) {
   return stream_supported(c->shape) && stream_few_tokens(c->blob.d, c->blob.I, static_cast<int>(c->blob.elem), T);
 }
 
-// Token batches with few rows per expert, streamed the same way from the device pair order instead of as grouped
-// GEMMs: bf16 weights, a mean of up to five rows.  us per pass, streamed against grouped: two layers of 128 experts,
-// d 2048, at 2.3 / 4 / 5 / 6.3 mean rows 423 / 490 / 537 / 612 against 543 / 562 / 569 / 570; 8 experts, d 4096,
-// at 4 / 5 / 7.8 rows 555 / 631 / 858 against 646 / 643 / 642.  fp8 rows cost the conversion of every code each:
-// 597 against 560 at two mean rows already.
-bool stream_rows_batch(const wisp_ctx* c, int32_t T) {
-  return c->desc.w_dtype == WISP_BF16 && stream_supported(c->shape) &&
-         static_cast<int64_t>(T) * c->k() <= 5 * static_cast<int64_t>(c->desc.n_experts);
+// Token batches with few rows per expert, streamed the same way from the device pair order instead of as grouped GEMMs.
+// cnt: pairs per expert of the whole layer-step, whatever part of it a launch holds, so that paged, resident and offloaded
+// runs choose alike.
+bool stream_rows_batch(const wisp_ctx* c, int32_t T, const std::vector<int32_t>& cnt) {
+  int64_t rows = 0, used = 0, items = 0;
+  auto add = [&](int32_t n) {
+    rows += n;
+    used += n > 0 ? 1 : 0;
+    items += (n + kStreamRows - 1) / kStreamRows;
+  };
+  for (int32_t n : cnt) add(n);
+  if (c->desc.has_shared) add(T);
+  const int64_t tiles = grouped_supported(c->shape, c->desc.has_shared) ? used * grouped_column_tiles(c->shape) : 0;
+  return stream_supported(c->shape) && stream_batch(c->blob.d, c->blob.I, static_cast<int>(c->blob.elem), rows, used, items, tiles);
 }
 
 // Token batches whose FFN runs as grouped GEMMs (a batch too long for the kernels' 32-bit offsets stays on the
@@ -682,7 +688,7 @@ wisp_status run_grouped(wisp_ctx* c, const std::vector<std::pair<int32_t, const 
   const uint64_t dI = static_cast<uint64_t>(B.d) * B.I;
   const uint64_t nb = B.w_dtype == DT_FP8 ? static_cast<uint64_t>(B.d / 128) * (B.I / 128) * 2 : 0;
   const bool f32_out = !grouped_supported(c->shape, c->desc.has_shared);
-  if (stream_rows_batch(c, T)) {
+  if (stream_rows_batch(c, T, cnt)) {
     std::vector<StreamItem> items;
     for (const auto& [e, w] : list) {
       const int32_t n = e < 0 ? T : cnt[e], at = e < 0 ? 0 : off[e];

@@ -462,6 +462,8 @@ bool grouped_supported(const FfnShape& s, int has_shared) {
          s.blob.d % kBR == 0 && s.blob.I % (kBR / 2) == 0;   // whole column tiles and K stages
 }
 
+int grouped_column_tiles(const FfnShape& s) { return s.blob.I / (kBR / 2); }
+
 namespace {
 // the buffer loads address x, h and an expert's weights by 32-bit byte offsets below kOutOfRange
 bool offsets_fit(const FfnShape& s, int n_tok, int k) {

@@ -87,7 +87,6 @@ hipError_t launch_down_combine_dev(const FfnBatch* plan, int max_items, const Ff
 // perm, packed in at (token of row i at bits 4 i, rank at bits 32 + 4 i: up to kStreamMaxTokens tokens); with
 // perm (the sorted pair order), perm[at .. at + rows), or, with kStreamShared, tokens at .. at + rows of the shared
 // expert.  h and buf rows are token * (k + 1) + rank, as for the per-item kernels; buf in fp32, or bf16 with bf16_out.
-constexpr int kStreamRows = 8;
 constexpr int kMaxStreamItems = 224;        // a kernel argument of under 4 KB
 constexpr uint64_t kStreamShared = 1ull << 32;
 struct StreamBatch {
@@ -140,6 +139,7 @@ struct GroupedBatch {
 // shared expert), and those whose grouped GEMMs (tile_gemm.hip) keep them in fp32, as the per-item kernels do:
 // fp8 weights, other widths, a shared expert.
 bool grouped_supported(const FfnShape& s, int has_shared);
+int grouped_column_tiles(const FfnShape& s);   // of an expert's gate/up in the first
 bool grouped_f32_supported(const FfnShape& s, int T, int k);
 // perm[off_e + i] = the i-th pair (ascending) routed to expert e; off_e = pairs of experts < e.
 // counts: device scratch of permute_segments(n_pairs) * N int32.  If totals is not NULL (N words of

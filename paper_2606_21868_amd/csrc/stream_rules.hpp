@@ -52,4 +52,29 @@ inline bool stream_few_tokens(int d, int I, int elem, int T) {
   return n >= (up.nl == 2 ? (eight_lanes ? 1200000 : 1500000) : (eight_lanes ? 450000 : 1000000));
 }
 
+// Token batches of bf16 layers (the alternative is a grouped GEMM, whose time hardly depends on the rows while they fit its
+// tiles): rows, over all experts of the layer-step that have any (used of them; a shared expert counts), at most c of them per
+// expert.  A row costs a sum over the lanes beside its products: the shorter the weight rows the sooner it outweighs the faster
+// stream; rows of more than five chunks per lane or of four waves run fewer waves at once.  tiles: the column tiles of
+// the grouped launch, kStreamChip of which run at a time (0: a form whose last round does not show); a last round that is not
+// full counts for the stream.  An expert of more than kStreamRows rows is read again for the next ones, which costs about as much
+// as four rows (64 experts of eight rows 138 us, of ten 195).  us per launch pair, streamed against grouped, in the order of c: d 512, I 512, 128 experts
+// by one / two rows 42 / 56 against 46 / 47; d 1024, I 1024, 128 by 3 / 4 137 / 157 against 146; d 1024, I 2816, 64 by 4 / 5
+// 207 / 232 against 204, 16 by 4 / 5 / 8 59 / 66 / 88 against 84; d 3072, I 1024, 64 by 3 / 4 196 / 222 against 212; d 5120, I 8192, 16
+// by 4 / 5 711 / 797 against 738; d 4096, I 14336, 8 by 4 / 5 490 / 537 against 556, 16 by 4 / 5 982 / 1081 against 958; d 2048,
+// I 768, 128 by 4 / 5 193 / 214 against 223, 64 by 6 / 8 122 / 138 against 133, 32 by 4 / 5 56 / 61 against 57, 16 by 32 119 against 53;
+// d 768, I 768, 128 by 5 86 against 96; d 1472, I 704 with a shared expert, 60 by 4 / 5 79 / 86 against 79.  fp8 rows cost the
+// conversion of every code each: 597 against 560 at two rows already (64 experts, d 7168).
+constexpr int kStreamChip = 256;
+constexpr int kStreamRows = 8;   // token rows of an expert that a launch takes with one read of its weights (an item)
+inline bool stream_batch(int d, int I, int elem, int64_t rows, int64_t used, int64_t items, int64_t tiles) {
+  StreamLanes up{}, dn{};
+  if (elem != 2 || !stream_lanes(d * elem / 16, &up) || !stream_lanes(I * elem / 16, &dn)) return false;
+  const int c2 = up.nl == 1 ? 0 : up.kw > 1 ? 8 : up.nl == 2 ? (dn.nl <= 2 ? 6 : 8) : up.nl <= 5 ? 11 : up.nl <= 7 ? 8 : 10;   // 2 c
+  rows += 4 * (items - used);
+  if (tiles <= kStreamChip) return 2 * rows <= c2 * used;
+  const int64_t rounds = (tiles + kStreamChip - 1) / kStreamChip;
+  return 2 * rows * tiles <= c2 * used * rounds * kStreamChip;
+}
+
 }  // namespace wisp

@@ -58,3 +58,27 @@ def test_router_forms_cover_every_row_and_column(ask):
     (7168, 384, 1, 4, False)])
 def test_few_tokens_form(ask, d, I, elem, T, stream):
     assert ask([("few", d, I, elem, T)])[0] == (int(stream),)
+
+
+# widths, bytes of a weight, rows of the layer-step, experts that have any (with equal shares), whether the grouped GEMM is the bf16 one of
+# 128-column tiles, and whether streaming beats it
+@pytest.mark.parametrize("d,I,elem,rows,used,grouped,stream", [
+    (2048, 768, 2, 296, 115, True, True), (2048, 768, 2, 640, 128, True, True), (2048, 768, 2, 705, 128, True, False),
+    (2048, 768, 2, 384, 64, True, True), (2048, 768, 2, 512, 64, True, False), (2048, 768, 2, 128, 32, True, True),
+    (2048, 768, 2, 256, 32, True, False), (2048, 768, 2, 128, 8, True, False), (2048, 768, 2, 512, 16, True, False),
+    (512, 512, 2, 256, 128, True, False), (512, 512, 2, 640, 128, True, False), (256, 128, 2, 64, 16, True, False),
+    (1024, 1024, 2, 384, 128, True, True), (1024, 1024, 2, 512, 128, True, False), (1024, 2816, 2, 256, 64, True, True),
+    (1024, 2816, 2, 320, 64, True, False), (1024, 2816, 2, 80, 16, True, True), (1024, 2816, 2, 128, 16, True, False),
+    (768, 768, 2, 640, 128, True, True), (3072, 1024, 2, 192, 64, True, True), (3072, 1024, 2, 320, 64, True, False),
+    (4096, 14336, 2, 40, 8, True, True), (4096, 14336, 2, 48, 8, True, False), (4096, 14336, 2, 32, 2, True, False),
+    (4096, 14336, 2, 96, 16, True, False), (5120, 8192, 2, 64, 16, True, True), (5120, 8192, 2, 80, 16, True, False),
+    (1472, 704, 2, 280, 61, False, True), (1472, 704, 2, 366, 61, False, False), (320, 192, 2, 60, 60, False, False),
+    (7168, 2048, 1, 128, 64, False, False)])
+def test_token_batch_form(ask, d, I, elem, rows, used, grouped, stream):
+    items = used * -(-rows // (8 * used))
+    assert ask([("batch", d, I, elem, rows, used, items, used * I // 128 if grouped else 0)])[0] == (int(stream),)
+
+
+def test_token_batch_form_counts_second_reads(ask):
+    # 640 rows of 128 experts stream while none has more than eight; with 60 experts read twice they do not
+    assert ask([("batch", 2048, 768, 2, 640, 128, i, 768) for i in (128, 188)]) == [(1,), (0,)]
