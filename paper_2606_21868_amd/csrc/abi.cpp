@@ -517,10 +517,16 @@ bool stream_rows_batch(const wisp_ctx* c, int32_t T, const std::vector<int32_t>&
 }
 
 // Token batches whose FFN runs as grouped GEMMs (a batch too long for the kernels' 32-bit offsets stays on the
-// per-item kernels where it ran on them before).
+// per-item kernels where it ran on them before; so does one whose rows are not on 16-byte boundaries, rows_fit).
 bool batch_gemm(const wisp_ctx* c, int32_t T) {
   return T >= kGroupedMinTokens &&
          (grouped_supported(c->shape, c->desc.has_shared) || grouped_f32_supported(c->shape, T, c->desc.top_k));
+}
+
+// The any-width grouped GEMMs move token rows straight into LDS, 16 bytes a lane, which takes aligned addresses only; every
+// other kernel loads them into registers, at any address.  (Rows are multiples of 128 bytes: one row tells for all.)
+bool rows_fit(const wisp_ctx* c, const void* x) {
+  return grouped_supported(c->shape, c->desc.has_shared) || reinterpret_cast<uintptr_t>(x) % 16 == 0;
 }
 
 // The fills of chunk ci on the side stream, in two halves with an event each (fill_ev[2 ci + h]).
@@ -1172,7 +1178,7 @@ wisp_status wisp_route_topk(wisp_ctx* ctx, int32_t layer, const void* x_dev, int
     const int n = T * d.top_k;
     // a token batch for the grouped FFN: its pairs are ordered by expert now, from the device ids,
     // while the host waits for the ids and pages the layer in (after the last reader of the order)
-    const bool early = batch_gemm(ctx, T);
+    const bool early = batch_gemm(ctx, T) && rows_fit(ctx, x_dev);
     if (early) {
       ctx->perm_layer = -1;
       if (ctx->perm_use_recorded) WISP_HIP(hipStreamWaitEvent(st, ctx->perm_use_ev, 0), "hipStreamWaitEvent(perm use)");
@@ -1306,7 +1312,7 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
   }
   off[0] = 0;
   for (int e = 0; e < N; ++e) off[e + 1] = off[e] + cnt[e];
-  const bool grouped = batch_gemm(ctx, T);
+  const bool grouped = batch_gemm(ctx, T) && rows_fit(ctx, x_dev);
   if (L.from_counts && (!grouped || ctx->perm_layer != layer || ctx->perm_T != T))
     return fail(WISP_E_STATE, "a page-in from device counts needs its layer's device permutation");
   if (!grouped) {   // the per-item launches list their pairs; the grouped ones read the device order
@@ -1652,7 +1658,8 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
   }
   // a token batch for the grouped FFN pages in from the device's per-expert counts (no prefetch
   // bookkeeping needs its ids)
-  const bool batch_counts = batch_gemm(ctx, T) && ctx->pf_mode == WISP_PREFETCH_OFF && ctx->cap >= 1;
+  const bool batch_counts = batch_gemm(ctx, T) && rows_fit(ctx, x_dev) && ctx->pf_mode == WISP_PREFETCH_OFF &&
+                            ctx->cap >= 1;
   for (int32_t l = 0; l < d.n_layers; ++l) {
     const void* xl = static_cast<const uint8_t*>(x_dev) + l * xs;
     int32_t* il = idx_dev + static_cast<size_t>(l) * T * d.top_k;
@@ -1865,7 +1872,7 @@ wisp_status wisp_offload_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32
       base = o.staging[b];
       WISP_HIP(hipStreamWaitEvent(sm, o.filled[b], 0), "hipStreamWaitEvent(staging fill)");
     }
-    if (batch_gemm(ctx, T) && !grouped_supported(ctx->shape, d.has_shared)) {
+    if (batch_gemm(ctx, T) && rows_fit(ctx, xl) && !grouped_supported(ctx->shape, d.has_shared)) {
       // the pager's grouped GEMMs, over the pair order wisp_route_topk enqueued on this stream
       std::vector<int32_t>& cnt = ctx->e_cnt;
       std::vector<int32_t>& off = ctx->e_off;

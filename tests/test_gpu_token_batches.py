@@ -66,3 +66,29 @@ def test_token_batch_offload_arms_give_the_same_bits(name):
             assert np.array_equal(out["y"].view(np.uint32), ref["y"].view(np.uint32)), mode
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("name", ["fp8", "bf16 shared"])
+def test_token_batch_at_any_address(name):
+    # hidden states two bytes past a 16-byte boundary: the direct-to-LDS loads do not take them, the per-item kernels do
+    wl, cap = CASES[name]
+    log(f"[case] unaligned rows {name} T={wl.T}")
+    run = wisp.DecodeRun(wl, device=0, steps=1)
+    try:
+        run.generate()
+        run.set_cap(cap)
+        ref = run.decode(record=True, steps=1)
+        n = run.x_dev.numel()
+        off = torch.zeros(n + 8, dtype=run.x_dev.dtype, device=run.dev)[1:1 + n].view(run.x_dev.shape)
+        assert off.data_ptr() % 16 == 2 and off.is_contiguous()
+        off.copy_(run.x_dev)
+        run.x_dev = off
+        run.ctx.set_profiling(1 << wisp.K_GROUPED_GATEUP)
+        out = run.decode(record=True, steps=1)
+        run.ctx.set_profiling(0)
+        assert run.ctx.kernel_times(wisp.K_GROUPED_GATEUP)["launches"] == 0
+        assert np.array_equal(out["idx"], ref["idx"]) and np.array_equal(out["w"], ref["w"])
+        err = np.abs(out["y"] - ref["y"]).max(-1) / np.abs(ref["y"]).max(-1)
+        assert err.max() <= 4e-2, err.max()   # each within 2e-2 of the oracle's row (parity.tolerance)
+    finally:
+        run.close()
