@@ -50,6 +50,9 @@ namespace {
   } while (0)
 
 constexpr size_t kMasterAlign = 4096;
+// Uploads of routed ids in flight before a forward waits for the first (the stream's own order is all the others need, so the
+// host runs that many layers ahead).
+constexpr int kIdsSlots = 4;
 
 struct TimedPair {
   hipEvent_t a, b;
@@ -122,12 +125,13 @@ struct wisp_ctx {
   uint64_t k_bytes[WISP_K_NUM] = {};
   uint64_t k_flops[WISP_K_NUM] = {};
   // token batches: the routed ids on the device and their expert-sorted order
-  int32_t* ids_up = nullptr;         // pinned staging of the ids for the upload
+  int32_t* ids_up = nullptr;         // pinned staging of the ids for the uploads: kIdsSlots of them, used in turn
   int32_t* d_ids = nullptr;          // [max_tokens * k]
   int32_t* d_perm = nullptr;         // [max_tokens * k]
   int32_t* d_perm_counts = nullptr;  // [segments of the pairs][N] scratch of the permutation
-  hipEvent_t ids_ev = nullptr;       // the last upload has been read
-  bool ids_ev_recorded = false;
+  hipEvent_t ids_ev[kIdsSlots] = {}; // a slot's last upload has been read
+  bool ids_ev_recorded[kIdsSlots] = {};
+  int ids_slot = 0;                  // the next upload's
   // the permutation of a token batch, computed from the device ids right after routing (while the
   // host pages the layer in) and used by the next wisp_moe_forward of that layer with the same ids
   hipEvent_t perm_ev = nullptr;      // the last early permutation is done
@@ -338,7 +342,7 @@ void free_ctx(wisp_ctx* c) {
   if (c->d_ids) (void)hipFree(c->d_ids);
   if (c->d_perm) (void)hipFree(c->d_perm);
   if (c->d_perm_counts) (void)hipFree(c->d_perm_counts);
-  if (c->ids_ev) (void)hipEventDestroy(c->ids_ev);
+  for (hipEvent_t e : c->ids_ev) if (e) (void)hipEventDestroy(e);
   if (c->perm_ev) (void)hipEventDestroy(c->perm_ev);
   if (c->perm_use_ev) (void)hipEventDestroy(c->perm_use_ev);
   for (void* p : {static_cast<void*>(c->d_pi), static_cast<void*>(c->d_pinv), static_cast<void*>(c->d_tau),
@@ -877,7 +881,7 @@ wisp_status wisp_create(const wisp_model_desc* desc, wisp_ctx** out) {
   c->batch_set.reserve(N);
   c->ids_scratch.resize(static_cast<size_t>(T) * k);
   const size_t pairs_bytes = sizeof(int32_t) * static_cast<size_t>(T) * k;
-  if (hipHostMalloc(&p, pairs_bytes, hipHostMallocDefault) != hipSuccess) return bail(WISP_E_NOMEM, "pinned scratch");
+  if (hipHostMalloc(&p, kIdsSlots * pairs_bytes, hipHostMallocDefault) != hipSuccess) return bail(WISP_E_NOMEM, "pinned scratch");
   c->ids_up = static_cast<int32_t*>(p);
   if (hipMalloc(&p, pairs_bytes) != hipSuccess) return bail(WISP_E_NOMEM, "scratch");
   c->d_ids = static_cast<int32_t*>(p);
@@ -886,8 +890,9 @@ wisp_status wisp_create(const wisp_model_desc* desc, wisp_ctx** out) {
   if (hipMalloc(&p, sizeof(int32_t) * static_cast<size_t>(permute_segments(T * k)) * N) != hipSuccess)
     return bail(WISP_E_NOMEM, "scratch");
   c->d_perm_counts = static_cast<int32_t*>(p);
-  if (hipEventCreateWithFlags(&c->ids_ev, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c->perm_ev, hipEventDisableTiming) != hipSuccess ||
+  for (hipEvent_t& e : c->ids_ev)
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return bail(WISP_E_HIP, "hipEventCreate failed");
+  if (hipEventCreateWithFlags(&c->perm_ev, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&c->perm_use_ev, hipEventDisableTiming) != hipSuccess)
     return bail(WISP_E_HIP, "hipEventCreate failed");
   c->e_cnt.assign(N, 0);
@@ -1351,12 +1356,15 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
       WISP_HIP(hipStreamWaitEvent(sm, ctx->perm_ev, 0), "hipStreamWaitEvent(perm)");
     if (!early) {
       // the ids go to the device; the permutation kernel orders the pairs by expert there
-      if (ctx->ids_ev_recorded) WISP_HIP(hipEventSynchronize(ctx->ids_ev), "hipEventSynchronize(ids)");
-      std::memcpy(ctx->ids_up, L.ids.data(), sizeof(int32_t) * n_pairs);
-      WISP_HIP(hipMemcpyAsync(ctx->d_ids, ctx->ids_up, sizeof(int32_t) * n_pairs, hipMemcpyHostToDevice, sm),
+      const int q = ctx->ids_slot;
+      int32_t* up = ctx->ids_up + static_cast<size_t>(q) * ctx->desc.max_tokens * k;
+      if (ctx->ids_ev_recorded[q]) WISP_HIP(hipEventSynchronize(ctx->ids_ev[q]), "hipEventSynchronize(ids)");
+      std::memcpy(up, L.ids.data(), sizeof(int32_t) * n_pairs);
+      WISP_HIP(hipMemcpyAsync(ctx->d_ids, up, sizeof(int32_t) * n_pairs, hipMemcpyHostToDevice, sm),
                "hipMemcpyAsync(ids)");
-      WISP_HIP(hipEventRecord(ctx->ids_ev, sm), "hipEventRecord(ids)");
-      ctx->ids_ev_recorded = true;
+      WISP_HIP(hipEventRecord(ctx->ids_ev[q], sm), "hipEventRecord(ids)");
+      ctx->ids_ev_recorded[q] = true;
+      ctx->ids_slot = (q + 1) % kIdsSlots;
       LaunchTiming tp = timing_begin(ctx, WISP_K_PERMUTE);
       WISP_HIP(launch_permute_pairs(ctx->d_ids, n_pairs, N, ctx->d_perm, ctx->d_perm_counts, sm, tp), "permute launch");
       timing_end(ctx, tp, WISP_K_PERMUTE, static_cast<uint64_t>(n_pairs) * 8);

@@ -92,3 +92,38 @@ def test_token_batch_at_any_address(name):
         assert err.max() <= 4e-2, err.max()   # each within 2e-2 of the oracle's row (parity.tolerance)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("name", ["fp8", "bf16 shared"])
+def test_forward_with_given_ids_does_not_wait_for_the_stream(name):
+    # page-in and forward with ids of the caller's own (no routing call): the host runs ahead of the stream, as with few tokens
+    wl, _ = CASES[name]
+    log(f"[case] forwards ahead of the stream {name} T={wl.T}")
+    run = wisp.DecodeRun(wl, device=0, steps=1)
+    try:
+        run.generate()
+        run.set_cap(wl.N)
+        run.ctx.preload()
+        ids = [np.stack([(np.arange(wl.k) + t + 3 * l) % wl.N for t in range(wl.T)]).astype(np.int32) for l in range(wl.L)]
+        g = torch.full((wl.T, wl.k), 1.0 / wl.k, device=run.dev)
+        y = torch.zeros((3, wl.L, wl.T, wl.d), device=run.dev)
+        a = torch.zeros((8192, 8192), dtype=torch.bfloat16, device=run.dev)
+        busy = torch.cuda.Event()
+
+        def step(i):
+            for l in range(wl.L):
+                run.ctx.page_in(l, ids[l], wl.T)
+                run.ctx.moe_forward(l, run.x_dev[0, l], wl.T, g, y[i, l], run.stream)
+        step(0)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(run.stream):
+            for _ in range(60):   # tens of milliseconds
+                a @ a
+            busy.record()
+        step(1)
+        assert not busy.query()
+        step(2)
+        torch.cuda.synchronize()
+        assert torch.equal(y[0], y[1]) and torch.equal(y[0], y[2])
+    finally:
+        run.close()
