@@ -235,11 +235,13 @@ wisp_status wisp_set_fusion(wisp_ctx* ctx, int32_t on);
 /* Kernel timing.  Launches of the classes whose bit is set in class_mask (1 << wisp_kernel_class;
  * 0 = off) are bracketed by HIP events on their own stream (kernels through the launch's own
  * start/stop events, fill batches by events on the side stream); durations accumulate per class.
+ * WISP_K_STREAMED has no launches of its own: the timed launches of the four FFN classes (2, 3, 6, 7) that ran the
+ * kernels which stream whole weight rows for a few token rows are counted there once more.
  * Classes: */
 typedef enum {
   WISP_K_ROUTER_LOGITS = 0, WISP_K_ROUTER_SELECT = 1, WISP_K_FFN_GATEUP = 2, WISP_K_FFN_DOWN = 3,
   WISP_K_COMBINE = 4, WISP_K_H2D_FILL = 5, WISP_K_GROUPED_GATEUP = 6, WISP_K_GROUPED_DOWN = 7,
-  WISP_K_PERMUTE = 8, WISP_K_DOWN_COMBINE = 9, WISP_K_NUM = 10
+  WISP_K_PERMUTE = 8, WISP_K_DOWN_COMBINE = 9, WISP_K_STREAMED = 10, WISP_K_NUM = 11
 } wisp_kernel_class;
 wisp_status wisp_set_profiling(wisp_ctx* ctx, int32_t class_mask);
 /* Waits for outstanding timed work, then returns the accumulated total milliseconds, number of

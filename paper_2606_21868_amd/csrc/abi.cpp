@@ -59,6 +59,7 @@ struct TimedPair {
   int kclass;
   uint64_t bytes;
   uint64_t flops;
+  bool streamed;   // counted as WISP_K_STREAMED too
 };
 
 struct LayerState {
@@ -216,9 +217,10 @@ LaunchTiming timing_begin(wisp_ctx* c, int kclass) {
   return t;
 }
 
-void timing_end(wisp_ctx* c, const LaunchTiming& t, int kclass, uint64_t bytes, uint64_t flops = 0) {
+void timing_end(wisp_ctx* c, const LaunchTiming& t, int kclass, uint64_t bytes, uint64_t flops = 0,
+                bool streamed = false) {
   if (!c->profiling || !t.start || !t.stop) return;
-  c->timed.push_back({t.start, t.stop, kclass, bytes, flops});
+  c->timed.push_back({t.start, t.stop, kclass, bytes, flops, streamed});
 }
 
 // Accumulate every finished timed pair; with wait, first wait for all of them.
@@ -233,10 +235,13 @@ void harvest(wisp_ctx* c, bool wait) {
     }
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, p.a, p.b) == hipSuccess) {
-      c->k_ms[p.kclass] += ms;
-      c->k_n[p.kclass] += 1;
-      c->k_bytes[p.kclass] += p.bytes;
-      c->k_flops[p.kclass] += p.flops;
+      for (int k : {p.kclass, static_cast<int>(WISP_K_STREAMED)}) {
+        if (k != p.kclass && !p.streamed) continue;
+        c->k_ms[k] += ms;
+        c->k_n[k] += 1;
+        c->k_bytes[k] += p.bytes;
+        c->k_flops[k] += p.flops;
+      }
     } else {
       (void)hipGetLastError();   // a pair that could not be timed must not leave an error for the next launch check
     }
@@ -622,10 +627,10 @@ wisp_status run_stream(wisp_ctx* c, const std::vector<StreamItem>& items, const 
     }
     LaunchTiming t1 = timing_begin(c, k_up);
     WISP_HIP(launch_stream_gateup(b, c->shape, x, perm, c->k(), c->h, st, t1), "streamed gate/up launch");
-    timing_end(c, t1, k_up, nw * (2 * n * B.elem + 2 * nb) + nt * (B.d + B.I) * 2, nt * 4 * n);
+    timing_end(c, t1, k_up, nw * (2 * n * B.elem + 2 * nb) + nt * (B.d + B.I) * 2, nt * 4 * n, true);
     LaunchTiming t2 = timing_begin(c, k_down);
     WISP_HIP(launch_stream_down(b, c->shape, c->h, perm, c->k(), c->buf, bf16_out, st, t2), "streamed down launch");
-    timing_end(c, t2, k_down, nw * (n * B.elem + nb) + nt * (B.I * 2 + B.d * (bf16_out ? 2 : 4)), nt * 2 * n);
+    timing_end(c, t2, k_down, nw * (n * B.elem + nb) + nt * (B.I * 2 + B.d * (bf16_out ? 2 : 4)), nt * 2 * n, true);
   }
   return WISP_OK;
 }
@@ -1585,8 +1590,8 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
     hipStream_t sm = static_cast<hipStream_t>(stream);
     const int max_items = T * d.top_k + d.has_shared;
     const int C = ctx->cap;
-    const bool stream = stream_tokens(ctx, T);
-    const bool dc = !stream && ctx->fusion && T == 1 && down_combine_supported(ctx->shape);
+    const bool streamed = stream_tokens(ctx, T);
+    const bool dc = !streamed && ctx->fusion && T == 1 && down_combine_supported(ctx->shape);
     for (int32_t l = 0; l < d.n_layers; ++l) {
       LayerState& L = ctx->layers[l];
       if (!L.wr) return fail(WISP_E_STATE, "router weights not set for this layer");
@@ -1623,14 +1628,14 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
       }
       LaunchTiming t3 = timing_begin(ctx, WISP_K_FFN_GATEUP);
       LaunchTiming t4 = dc ? LaunchTiming{} : timing_begin(ctx, WISP_K_FFN_DOWN);
-      if (stream)
+      if (streamed)
         WISP_HIP(launch_stream_dev(ctx->d_plan, max_items, ctx->shape, xl, ctx->h, ctx->buf, sm, t3, t4),
                  "device-planned FFN launch");
       else
         WISP_HIP(launch_ffn_dev(ctx->d_plan, max_items, ctx->shape, xl, ctx->h, ctx->buf, !dc, T == 1, sm, t3, t4),
                  "device-planned FFN launch");
-      timing_end(ctx, t3, WISP_K_FFN_GATEUP, 0);
-      if (!dc) timing_end(ctx, t4, WISP_K_FFN_DOWN, 0);
+      timing_end(ctx, t3, WISP_K_FFN_GATEUP, 0, 0, streamed);
+      if (!dc) timing_end(ctx, t4, WISP_K_FFN_DOWN, 0, 0, streamed);
       if (dc) {
         LaunchTiming t5 = timing_begin(ctx, WISP_K_DOWN_COMBINE);
         WISP_HIP(launch_down_combine_dev(ctx->d_plan, max_items, ctx->shape, ctx->h, wl, yl, d.top_k, d.has_shared, sm,
@@ -1898,24 +1903,24 @@ wisp_status wisp_offload_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32
       WISP_HIP(hipEventRecord(ctx->perm_use_ev, sm), "hipEventRecord(perm use)");
       ctx->perm_use_recorded = true;
     } else {
-    // the routed experts of the layer, ascending, each with its (token, rank) pairs
-    std::vector<Work> work;
-    for (int e = 0; e < d.n_experts; ++e) {
-      Work wk;
-      for (int32_t t = 0; t < T; ++t)
-        for (int j = 0; j < k; ++j)
-          if (ids[t * k + j] == e) wk.pairs.push_back({t, t * rows + j});
-      if (wk.pairs.empty()) continue;
-      wk.w = base + static_cast<size_t>(e) * ctx->master_stride;
-      work.push_back(std::move(wk));
-    }
-    if (d.has_shared) {
-      Work wk;
-      wk.w = ctx->layers[l].shared_dev;
-      for (int32_t t = 0; t < T; ++t) wk.pairs.push_back({t, t * rows + k});
-      work.push_back(std::move(wk));
-    }
-    if ((s = run_ffn(ctx, work, xl, T, sm)) != WISP_OK) return s;
+      // the routed experts of the layer, ascending, each with its (token, rank) pairs
+      std::vector<Work> work;
+      for (int e = 0; e < d.n_experts; ++e) {
+        Work wk;
+        for (int32_t t = 0; t < T; ++t)
+          for (int j = 0; j < k; ++j)
+            if (ids[t * k + j] == e) wk.pairs.push_back({t, t * rows + j});
+        if (wk.pairs.empty()) continue;
+        wk.w = base + static_cast<size_t>(e) * ctx->master_stride;
+        work.push_back(std::move(wk));
+      }
+      if (d.has_shared) {
+        Work wk;
+        wk.w = ctx->layers[l].shared_dev;
+        for (int32_t t = 0; t < T; ++t) wk.pairs.push_back({t, t * rows + k});
+        work.push_back(std::move(wk));
+      }
+      if ((s = run_ffn(ctx, work, xl, T, sm)) != WISP_OK) return s;
     }
     LaunchTiming tc = timing_begin(ctx, WISP_K_COMBINE);
     WISP_HIP(launch_combine(T, k, d.d_model, d.has_shared, wl, ctx->buf, yl, sm, tc), "combine launch");

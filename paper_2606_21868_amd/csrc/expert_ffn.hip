@@ -921,12 +921,12 @@ hipError_t launch_ffn_dev(const FfnBatch* plan, int max_items, const FfnShape& s
                           static_cast<uint32_t>(L.off_w3), static_cast<uint32_t>(L.off_w2),
                           static_cast<uint32_t>(L.bytes - L.off_w2), static_cast<uint8_t*>(h));
   else
-  hipExtLaunchKernelGGL(gk, dim3(max_items * bpi), dim3(256), static_cast<uint32_t>(lds_g), st, tm_gateup.start,
-                        tm_gateup.stop, 0, plan, static_cast<const uint8_t*>(x), L.d, L.I, bpi, rows_hit, fault_wgs,
-                        copy_wgs, static_cast<uint32_t>(L.off_w1), static_cast<uint32_t>(L.off_w3),
-                        static_cast<uint32_t>(L.off_s1), static_cast<uint32_t>(L.off_s3),
-                        static_cast<uint32_t>(L.off_w2), static_cast<uint32_t>(L.bytes - L.off_w2),
-                        static_cast<uint8_t*>(h));
+    hipExtLaunchKernelGGL(gk, dim3(max_items * bpi), dim3(256), static_cast<uint32_t>(lds_g), st, tm_gateup.start,
+                          tm_gateup.stop, 0, plan, static_cast<const uint8_t*>(x), L.d, L.I, bpi, rows_hit, fault_wgs,
+                          copy_wgs, static_cast<uint32_t>(L.off_w1), static_cast<uint32_t>(L.off_w3),
+                          static_cast<uint32_t>(L.off_s1), static_cast<uint32_t>(L.off_s3),
+                          static_cast<uint32_t>(L.off_w2), static_cast<uint32_t>(L.bytes - L.off_w2),
+                          static_cast<uint8_t*>(h));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !with_down) return e;
   // down: per item slot, one row pass per workgroup

@@ -332,10 +332,12 @@ Kern kernel_of(const Shape& s, int* rows_per_wg) {
     *rows_per_wg = 4 / W * (64 / L) * rp;                   \
     return &stream_kernel<WT, MODE, L, N, rp, W>;           \
   }
-  WISP_S(64, 1, 1) WISP_S(64, 2, 1) WISP_S(64, 3, 1) WISP_S(64, 4, 1) WISP_S(64, 5, 1) WISP_S(64, 6, 1)
-  WISP_S(64, 7, 1) WISP_S(64, 8, 1) WISP_S(32, 1, 1) WISP_S(32, 3, 1) WISP_S(32, 5, 1) WISP_S(16, 1, 1)
-  WISP_S(16, 3, 1) WISP_S(64, 3, 4) WISP_S(64, 4, 4) WISP_S(64, 5, 4) WISP_S(64, 6, 4) WISP_S(64, 7, 4)
-  WISP_S(64, 8, 4)
+  if constexpr (MODE == MODE_DN) {   // (one chunk per lane of a gate/up row: such layers do not stream)
+    WISP_S(64, 1, 1) WISP_S(32, 1, 1) WISP_S(16, 1, 1)
+  }
+  WISP_S(64, 2, 1) WISP_S(64, 3, 1) WISP_S(64, 4, 1) WISP_S(64, 5, 1) WISP_S(64, 6, 1) WISP_S(64, 7, 1)
+  WISP_S(64, 8, 1) WISP_S(32, 3, 1) WISP_S(32, 5, 1) WISP_S(16, 3, 1) WISP_S(64, 3, 4) WISP_S(64, 4, 4)
+  WISP_S(64, 5, 4) WISP_S(64, 6, 4) WISP_S(64, 7, 4) WISP_S(64, 8, 4)
 #undef WISP_S
   return nullptr;
 }

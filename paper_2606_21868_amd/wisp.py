@@ -27,9 +27,10 @@ LINK_COPY_ENGINE, LINK_CUS = 0, 1
 OFFLOAD_BULK, OFFLOAD_ZERO_COPY = 0, 1
 PREFETCH_OFF, PREFETCH_PREDICTOR, PREFETCH_HINTS = 0, 1, 2
 (K_ROUTER_LOGITS, K_ROUTER_SELECT, K_FFN_GATEUP, K_FFN_DOWN, K_COMBINE, K_H2D_FILL, K_GROUPED_GATEUP,
- K_GROUPED_DOWN, K_PERMUTE, K_DOWN_COMBINE) = range(10)
+ K_GROUPED_DOWN, K_PERMUTE, K_DOWN_COMBINE, K_STREAMED) = range(11)
 KERNEL_CLASS_NAMES = ["router_logits", "router_select", "ffn_gateup", "ffn_down", "combine", "h2d_fill",
-                      "grouped_gateup", "grouped_down", "permute", "down_combine"]
+                      "grouped_gateup", "grouped_down", "permute", "down_combine",
+                      "streamed"]   # the last: FFN launches of the streamed-row kernels, counted once more
 
 
 class WispError(RuntimeError):

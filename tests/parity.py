@@ -253,10 +253,12 @@ def check_slots_hold_masters(run, max_bytes=4e9):
 
 
 def run_case(wl, cap, steps, sample_points=None, check_all_outputs=False, tokens=None, expect_grouped=None,
-             pageable=False):
+             pageable=False, expect_streamed=None):
     """Paged run from a cold table, checked against the oracle (routing, pager, outputs at all or the
     sampled (step, layer) points, optionally on a subset of tokens); the device pager where it
-    applies; then the fully resident run (C = N, preloaded) must give bit-identical outputs."""
+    applies; then the fully resident run (C = N, preloaded) must give bit-identical outputs.  expect_grouped: the
+    token-batch path (pairs ordered on the device) or the one of a few tokens; expect_streamed: whether either's launches
+    were those of the streamed-row kernels."""
     import pytest
 
     from paper_2606_21868_amd import wisp
@@ -275,7 +277,10 @@ def run_case(wl, cap, steps, sample_points=None, check_all_outputs=False, tokens
             n_grouped = run.ctx.kernel_times(wisp.K_GROUPED_GATEUP)["launches"]
             n_items = run.ctx.kernel_times(wisp.K_FFN_GATEUP)["launches"]
             assert (n_grouped > 0, n_items > 0) == (expect_grouped, not expect_grouped), (n_grouped, n_items)
-            log(f"  expert FFN path: {'grouped MFMA GEMMs' if expect_grouped else 'per-item GEMV'} "
+            n_streamed = run.ctx.kernel_times(wisp.K_STREAMED)["launches"]
+            if expect_streamed is not None:
+                assert n_streamed == (n_grouped + n_items if expect_streamed else 0), (n_streamed, n_grouped, n_items)
+            log(f"  expert FFN path: {'streamed rows' if n_streamed else 'grouped MFMA GEMMs' if expect_grouped else 'per-item GEMV'} "
                 f"({n_grouped + n_items} gate/up launches)")
         log("  oracle routing")
         ora_idx, ora_g, margin, gmargin, scores = oracle_routing(run, steps)
