@@ -14,7 +14,7 @@ __global__ void __launch_bounds__(NW * 64, 2) tile_kernel(GroupedBatch gb, const
                                                           uint32_t a_bytes, const int32_t* __restrict__ perm, int k,
                                                           int d, int I, uint32_t off0, uint32_t off1, uint32_t soff0,
                                                           uint32_t soff1, uint32_t w_bytes, void* __restrict__ out) {
-  tile::tile_body<WT, MODE, NW, RB, true>(gb, a_src, a_bytes, perm, k, d, I, off0, off1, soff0, soff1, w_bytes, out);
+  tile::tile_body<WT, MODE, NW, RB>(gb, a_src, a_bytes, perm, k, d, I, off0, off1, soff0, soff1, w_bytes, out);
 }
 
 template <int WT, int MODE, int NW, int RB>

@@ -66,7 +66,7 @@ __device__ __forceinline__ int32_t load_i32(const int32_t* p) {
   asm volatile("global_load_dword %0, %1, off" : "=&v"(v) : "v"(p) : "memory");
   return v;
 }
-__device__ __forceinline__ void pin_i32(int32_t& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void pin_i32(int32_t& v) { asm volatile("; pin %0" : "+v"(v)); }
 __device__ __forceinline__ void lds_write_i32(uint32_t addr, int32_t v) {
   asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(v) : "memory");
 }
@@ -154,8 +154,8 @@ __device__ __forceinline__ u32x4_t rsrc_words(const void* p, uint32_t bytes) {
   r.w = 0x00020000u;
   return r;
 }
-// WT weights, NW waves, RB token rows per row block, OUT32: fp32 outputs (else bf16).
-template <int WT, int MODE, int NW, int RB, bool OUT32>
+// WT weights, NW waves, RB token rows per row block.
+template <int WT, int MODE, int NW, int RB>
 __device__ __forceinline__ void tile_body(const GroupedBatch& gb, const uint16_t* __restrict__ a_src, uint32_t a_bytes,
                                           const int32_t* __restrict__ perm, int k, int d, int I, uint32_t off0,
                                           uint32_t off1, uint32_t soff0, uint32_t soff1, uint32_t w_bytes,
@@ -332,11 +332,7 @@ __device__ __forceinline__ void tile_body(const GroupedBatch& gb, const uint16_t
           for (int i = 0; i < 4; ++i) {
             if (s * 16 + g * 4 + i < n_rows) {
               const size_t o = static_cast<size_t>(orow[i]) * d + col;
-              if constexpr (OUT32)
-                *reinterpret_cast<float2*>(static_cast<float*>(out) + o) = make_float2(acc[0][s][i], acc[1][s][i]);
-              else
-                *reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(out) + o) =
-                    bf16_rne(acc[0][s][i]) | (static_cast<uint32_t>(bf16_rne(acc[1][s][i])) << 16);
+              *reinterpret_cast<float2*>(static_cast<float*>(out) + o) = make_float2(acc[0][s][i], acc[1][s][i]);
             }
           }
         }
