@@ -635,25 +635,24 @@ wisp_status run_stream(wisp_ctx* c, const std::vector<StreamItem>& items, const 
   return WISP_OK;
 }
 
-// Items of up to kStreamRows pairs from work lists (tokens below 16).
-std::vector<StreamItem> stream_items(const std::vector<Work>& work, int rows_per_token) {
-  std::vector<StreamItem> items;
-  for (const Work& wk : work)
-    for (size_t p0 = 0; p0 < wk.pairs.size(); p0 += kStreamRows) {
-      StreamItem it{wk.w, 0, static_cast<int32_t>(std::min<size_t>(kStreamRows, wk.pairs.size() - p0))};
-      for (int q = 0; q < it.rows; ++q) {
-        const Pair& p = wk.pairs[p0 + q];
-        it.at |= static_cast<uint64_t>(p.t) << (4 * q) | static_cast<uint64_t>(p.out % rows_per_token) << (32 + 4 * q);
-      }
-      items.push_back(it);
-    }
-  return items;
+// Appends row i of the expert at w (its i-th pair: token t below 16, rank) to the items.
+void add_row(std::vector<StreamItem>& items, const uint8_t* w, int32_t i, int32_t t, int32_t rank) {
+  if (i % kStreamRows == 0) items.push_back({w, 0, 0});
+  StreamItem& it = items.back();
+  it.at |= static_cast<uint64_t>(t) << (4 * it.rows) | static_cast<uint64_t>(rank) << (32 + 4 * it.rows);
+  ++it.rows;
 }
 
 wisp_status run_ffn(wisp_ctx* c, const std::vector<Work>& work, const void* x, int32_t T, hipStream_t st,
                     bool down = true) {
-  if (stream_tokens(c, T))
-    return run_stream(c, stream_items(work, c->k() + 1), x, nullptr, false, WISP_K_FFN_GATEUP, WISP_K_FFN_DOWN, st);
+  if (stream_tokens(c, T)) {
+    std::vector<StreamItem>& items = c->items[0];
+    items.clear();
+    for (const Work& wk : work)
+      for (size_t i = 0; i < wk.pairs.size(); ++i)
+        add_row(items, wk.w, static_cast<int32_t>(i), wk.pairs[i].t, wk.pairs[i].out % (c->k() + 1));
+    return run_stream(c, items, x, nullptr, false, WISP_K_FFN_GATEUP, WISP_K_FFN_DOWN, st);
+  }
   FfnBatch b;
   b.n_items = 0;
   b.max_ntok = 0;
@@ -1445,20 +1444,12 @@ wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, in
         const int32_t e = cp.experts[i];
         std::vector<StreamItem>& to = items[cp.fault[i] ? 1 + L.late[ci][i] : 0];
         for (int32_t q = off[e]; q < off[e + 1]; ++q) {
-          const int32_t p = ctx->pair_order[q], i0 = (q - off[e]) % kStreamRows, t = p / k;
-          if (i0 == 0) to.push_back({L.chunk_ptrs[ci][i], 0, 0});
-          StreamItem& it = to.back();
-          it.at |= static_cast<uint64_t>(t) << (4 * i0) | static_cast<uint64_t>(p - t * k) << (32 + 4 * i0);
-          it.rows = i0 + 1;
+          const int32_t p = ctx->pair_order[q], t = p / k;
+          add_row(to, L.chunk_ptrs[ci][i], q - off[e], t, p - t * k);
         }
       }
       if (ci == 0 && ctx->desc.has_shared)
-        for (int32_t t = 0; t < T; ++t) {
-          if (t % kStreamRows == 0) items[0].push_back({L.shared_dev, 0, 0});
-          StreamItem& it = items[0].back();
-          it.at |= static_cast<uint64_t>(t) << (4 * it.rows) | static_cast<uint64_t>(k) << (32 + 4 * it.rows);
-          ++it.rows;
-        }
+        for (int32_t t = 0; t < T; ++t) add_row(items[0], L.shared_dev, t, t, k);
       auto run = [&](const std::vector<StreamItem>& v) {
         return run_stream(ctx, v, x_dev, nullptr, false, WISP_K_FFN_GATEUP, WISP_K_FFN_DOWN, sm);
       };

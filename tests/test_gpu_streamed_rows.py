@@ -105,6 +105,29 @@ def test_token_batch_with_skewed_routing_runs_grouped():
         run.close()
 
 
+@pytest.mark.parametrize("name", ["bf16 64x3+ 32x3+, shared", "fp8 64x3+ 16x3"])
+def test_offload_arm_streams_the_same_bits(name):
+    # the static-offload arm builds its items from work lists; an expert of more than eight rows among them
+    wl = CASES[name][0].with_(L=1)
+    log(f"[case] offload arm {name}")
+    run = wisp.DecodeRun(wl, device=0, steps=1)
+    try:
+        run.generate()
+        run.set_cap(wl.N)
+        run.ctx.preload()
+        ref = run.decode(record=True, steps=1)
+        run.ctx.offload_begin(wl.N * ((run.blob_bytes + 4095) // 4096 * 4096), wisp.OFFLOAD_ZERO_COPY)
+        run.ctx.set_profiling(1 << wisp.K_FFN_GATEUP)
+        out = run.offload(record=True, steps=1)
+        run.ctx.set_profiling(0)
+        run.ctx.offload_end()
+        assert run.ctx.kernel_times(wisp.K_STREAMED)["launches"] > 0
+        assert np.array_equal(out["idx"], ref["idx"])
+        assert np.array_equal(out["y"].view(np.uint32), ref["y"].view(np.uint32))
+    finally:
+        run.close()
+
+
 # Rows whose chunks do not fill their lanes (in one wave, over four waves, fp8), with an infinite weight or block scale in the
 # last chunk: what lies past a row's end must not turn the infinity into a NaN.  One expert alone holds infinities; fp8 codes and
 # inputs are made positive so that every infinite term has one sign.
