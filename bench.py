@@ -33,7 +33,8 @@ Reported beside the throughput:
                  cap): tokens/s of a cold pass against T_roof = fault bytes / link + max(HBM bytes /
                  8 TB/s, FLOPs / 2.5 PFLOP/s), and the matrix-core rate of the grouped GEMMs in a
                  fully resident pass.
-Usage: python bench.py [--gpus 1] [--steps K] [--warmup W]
+The line printed holds the headline of each (a few KB); --detail FILE keeps everything measured.
+Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--detail FILE]
 """
 from __future__ import annotations
 
@@ -506,7 +507,8 @@ def pageable_leg(wisp, torch, name, warmup, steps, cpu=True):
         if g["launches"]:
             gbps = g["bytes"] / (g["total_ms"] * 1e-3) / 1e9
             tr = measured_traffic(wl.name, "ffn_gateup")
-            gate = dict(bound="hbm", kernel="ffn_rows expert gate/up (W1+W3 rows" +
+            streamed = run.ctx.kernel_times(wisp.K_STREAMED)["launches"] > 0
+            gate = dict(bound="hbm", kernel=f"{'stream_kernel' if streamed else 'ffn_rows'} expert gate/up (W1+W3 rows" +
                         (", fp8 E4M3 x bf16 block scales" if wl.w_dtype == wisp.FP8 else ", bf16") + "), timed region",
                         achieved=gbps, peak=HBM_PEAK_GBPS, unit="GB/s", frac=gbps / HBM_PEAK_GBPS,
                         launches=g["launches"], avg_launch_us=g["total_ms"] * 1e3 / g["launches"],
@@ -653,6 +655,38 @@ def prefill_leg(wisp, torch, link, link_cu, passes=3):
         run.close()
 
 
+def pick(d, *keys):
+    """The named entries of d that it has (None if d is None), numbers to seven digits."""
+    if d is None:
+        return None
+    num = lambda v: float(f"{v:.7g}") if isinstance(v, float) else v
+    return {k: num(d[k]) for k in keys if k in d}
+
+
+def summary(r):
+    """The printed line of the full result r: the contract's keys as they are, and of each leg its headline."""
+    line = {k: r[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                              "vs_baseline", "dtype", "data", "config")}
+    line["roofline"] = pick(r["roofline"], "bound", "achieved", "peak", "unit", "frac", "traffic", "kernel", "avg_launch_us",
+                            "bytes_per_launch", "launches", "frac_of_read_floor")
+    line["path_roofline"] = pick(r["path_roofline"], "frac", "roofline_tokens_per_s", "link_engine", "link_GBps_measured",
+                                 "faults_per_token", "fault_rate")
+    line["cpu_baseline"] = pick(r["cpu_baseline"], "value", "unit", "cores", "kind", "sample")
+    line["pager"] = r["pager"]
+    line["passes"] = {n: dict(pick(p, "tokens_per_s", "ms_per_step"), frac=pick(p["path_roofline"], "frac")["frac"])
+                      for n, p in r["passes"].items()}
+    if r["prefill"]:
+        line["prefill"] = dict(pick(r["prefill"], "tokens_per_s", "pass_ms", "cap_per_layer", "faults"),
+                               frac=pick(r["prefill"]["roofline"], "frac")["frac"],
+                               resident=pick(r["prefill"]["resident"], "tokens_per_s", "pass_ms"))
+    if r["sweep"]:
+        line["sweep"] = [pick(c, "cap", "paged_tokens_per_s", "speedup_vs_zero_copy", "speedup_vs_bulk") for c in r["sweep"]]
+    if r["pageable_legs"]:
+        line["pageable_legs"] = {n: dict(pick(v, "tokens_per_s"), frac=pick(v["path_roofline"], "frac")["frac"])
+                                 for n, v in r["pageable_legs"].items()}
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
     ap.add_argument("--gpus", type=int, default=1)
@@ -674,6 +708,7 @@ def main():
                     help="separate down and combine kernels instead of the fused down+combine (single-token steps)")
     ap.add_argument("--census-steps", type=int, default=24,
                     help="extra decode steps after the timed region with every kernel class timed (0 = skip)")
+    ap.add_argument("--detail", default=None, help="also write everything measured to this file (JSON)")
     args = ap.parse_args()
 
     world = int(os.environ.get("WORLD_SIZE", "1"))
@@ -918,7 +953,10 @@ def main():
         "prefetch": prefetch,
         "pageable_legs": pageable,
     }
-    print(json.dumps(result), flush=True)
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(result, f, indent=1)
+    print(json.dumps(summary(result)), flush=True)
 
 
 if __name__ == "__main__":
