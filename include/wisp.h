@@ -167,9 +167,11 @@ wisp_status wisp_page_in(wisp_ctx* ctx, int32_t layer, const int32_t* ids_host, 
  * fp32, y_dev [T, d] fp32, on `stream`.  Returns WISP_E_NOT_RESIDENT if a routed expert is not
  * resident (exactness invariant, Sec. 3.2).  st (optional) receives the step's counts.  Precision:
  * fp32 accumulation; with bf16 or fp8 weights h is rounded to bf16.  Token batches of 16 or more
- * tokens run as grouped matrix-core GEMMs; with bf16 weights, d_model a multiple of 256, d_ff of 128 and
- * no shared expert they also round each o_tj to bf16 before the combine (every other shape, and
- * smaller batches, keep o_tj in fp32). */
+ * tokens run as grouped matrix-core GEMMs, or, with bf16 weights and few token rows per expert that is routed to, on
+ * kernels that stream whole weight rows; with bf16 weights, d_model a multiple of 256, d_ff of 128 and no shared expert
+ * either also rounds each o_tj to bf16 before the combine (every other shape, and smaller batches, keep o_tj in fp32).
+ * (Every shape but that one runs batches of 16 or more tokens several times slower when x_dev is not on a 16-byte
+ * boundary.) */
 wisp_status wisp_moe_forward(wisp_ctx* ctx, int32_t layer, const void* x_dev, int32_t T, const float* w_dev,
                              float* y_dev, void* stream, wisp_page_stats* st);
 
@@ -292,7 +294,7 @@ wisp_status wisp_decode_fp8(const uint8_t* codes_dev, float* out_dev, int32_t n,
  * without a context.  Routes T tokens x_dev [T, d] (x_dtype WISP_F32 or WISP_BF16) with router weights
  * w_r_dev [N, d] fp32 row-major into idx_dev [T, k] int32 and w_dev [T, k] fp32 on `stream`, ranks
  * ordered (score desc, expert id asc), route / n_groups / topk_groups as in wisp_model_desc.  It runs
- * the same kernels as wisp_route_topk with fusion on (one launch for T <= 4, logits then selection
+ * the arithmetic of wisp_route_topk, value by value (one launch for T <= 4, logits then selection
  * above), so ids and gates are bit-identical to it; nothing is published to the host.
  * Allocates nothing: its scratch (the tagged logit words of the one-launch path, and the logits, kept
  * for token batches as up to eight partial sums over column slices) is a fixed device array of

@@ -9,8 +9,9 @@
 // W3 (gate/up) or RP rows of W2 (down) at once, about 16 loads in flight per lane, issued before anything
 // else, and holds them in registers while it goes through the expert's token rows.  A token costs 4
 // v_dot2_f32_bf16 per chunk (8 with fp8: codes converted exactly to bf16, pairs summed in fp32, times
-// the chunk's block scale in fp32) and a butterfly over the lanes that halves the values as it goes.  No LDS, no barrier;
-// one launch takes every expert.  A row's chain depends on the shape alone, so a result has the same bits
+// the chunk's block scale in fp32) and a butterfly over the lanes that halves the values as it goes.  No LDS and no
+// barrier, except where four waves share a row: their sums of a token meet in LDS.  A launch takes up to 224 items.
+// Token rows go one after the other, each a round trip for its inputs: which layers and batches stream is stream_rules.hpp's.  A row's chain depends on the shape alone, so a result has the same bits
 // whichever launch holds its expert.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>

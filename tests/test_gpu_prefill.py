@@ -60,7 +60,7 @@ def test_prefill_below_grouped_threshold():
 
 
 def test_prefill_router_rows_not_multiple_of_16():
-    # 24 experts: the token-batch router takes its LDS-tiled FMA kernel instead of the matrix cores
+    # 24 experts: the token-batch router's matrix-core tiles reach past the last router row
     wl = WORKLOADS["qwen3-30b-a3b-prefill"].with_(L=2, T=40, d=256, I=128, N=24, k=4)
     run_case(wl, 7, 1, check_all_outputs=True, expect_grouped=True)
 
