@@ -177,6 +177,8 @@ struct wisp_ctx {
   bool fusion = true;                // fused decode kernels (route + page; down + combine)
   uint64_t* d_logit_tags = nullptr;  // [kRouteSelectTokens][N] tagged logit words of the one-launch router kernels
   uint32_t logit_tag = 0;            // tag of the last such launch (never 0)
+  bool tags_pending = false;         // it was left on tags_stream with nothing waited for
+  hipStream_t tags_stream = nullptr;
   // speculative prefetch inside wisp_decode_step (host pager)
   int32_t pf_mode = WISP_PREFETCH_OFF;
   wisp_predictor* pf_pred = nullptr;
@@ -255,6 +257,16 @@ void harvest(wisp_ctx* c, bool wait) {
 uint32_t next_logit_tag(wisp_ctx* c) {
   if (++c->logit_tag == 0) ++c->logit_tag;
   return c->logit_tag;
+}
+
+// The tag words belong to one launch at a time: the streams' own order keeps launches on one stream apart, a wait those on two
+// (a launch whose words another overwrites would wait for its tag for ever).  waited: the host waits for this launch's results.
+hipError_t claim_logit_tags(wisp_ctx* c, hipStream_t st, bool waited) {
+  hipError_t e = hipSuccess;
+  if (c->tags_pending && c->tags_stream != st) e = hipDeviceSynchronize();
+  c->tags_pending = !waited;
+  c->tags_stream = st;
+  return e;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1137,8 +1149,9 @@ namespace {
 wisp_status route_kernels(wisp_ctx* ctx, LayerState& L, const void* x_dev, int32_t T, int32_t* idx_dev, float* w_dev,
                           uint64_t* idx_tagged, uint32_t seq, hipStream_t st) {
   const auto& d = ctx->desc;
-  if (ctx->fusion && T <= kRouteSelectTokens && (T + 3) / 4 <= d.n_experts) {
-    // logits and selection in one launch (a workgroup per four tokens selects once every row is published)
+  if (ctx->fusion && T <= kRouteSelectTokens && (T + 3) / 4 <= d.n_experts && (idx_tagged || !stream_capturing(st))) {
+    // logits and selection in one launch (the first workgroups select once every row is published)
+    WISP_HIP(claim_logit_tags(ctx, st, idx_tagged != nullptr), "wait for the routing on another stream");
     LaunchTiming t1 = timing_begin(ctx, WISP_K_ROUTER_SELECT);
     WISP_HIP(launch_route_select(L.wr, x_dev, d.x_dtype, d.d_model, ctx->d_logit_tags, next_logit_tag(ctx),
                                  T, d.n_experts,
@@ -1595,6 +1608,7 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
       uint64_t* tau_l = ctx->d_tau + static_cast<size_t>(l) * C;
       const uint64_t* slot_l = ctx->d_slot_ptr + static_cast<size_t>(l) * C;
       if (ctx->fusion) {
+        WISP_HIP(claim_logit_tags(ctx, sm, false), "wait for the routing on another stream");
         LaunchTiming t1 = timing_begin(ctx, WISP_K_ROUTER_SELECT);
         WISP_HIP(launch_route_page(L.wr, xl, d.x_dtype, d.d_model, ctx->d_logit_tags, next_logit_tag(ctx),
                                    T, d.n_experts, d.top_k,
@@ -1642,6 +1656,7 @@ wisp_status wisp_decode_step(wisp_ctx* ctx, const void* x_dev, int32_t T, int32_
     WISP_HIP(hipMemcpyAsync(ctx->h_stats, ctx->d_stats, sizeof(uint32_t) * 2 * d.n_layers, hipMemcpyDeviceToHost, sm),
              "stats copy");
     WISP_HIP(hipStreamSynchronize(sm), "hipStreamSynchronize");
+    ctx->tags_pending = false;
     if (ctx->profiling) harvest(ctx, false);
     for (int32_t l = 0; l < d.n_layers; ++l) {
       wisp_page_stats ps{};

@@ -173,7 +173,8 @@ hipError_t launch_router_logits(const float* wr, const void* x, int x_dtype, int
 // four tokens selects once every row is published); the same ids, gates and tagged ids as
 // launch_router_logits + launch_router_select.  logits: [T, N] 64-bit words where the rows are published tagged with `tag`, which
 // must differ from the tag of the launch that last wrote them (a per-launch sequence number, never 0;
-// the words start at 0).
+// the words start at 0).  So no other launch may write the words while one runs (its selection waits for its own tag), and a
+// captured launch, whose tag every replay repeats, would take the replay's before for its own: neither is for this kernel.
 constexpr int kRouteSelectTokens = 8;
 hipError_t launch_route_select(const float* wr, const void* x, int x_dtype, int d, uint64_t* logits, uint32_t tag,
                                int T, int N, int k, int route, int n_groups, int topk_groups,
@@ -200,6 +201,14 @@ hipError_t launch_route_page(const float* wr, const void* x, int x_dtype, int d,
                              const uint64_t* slot_ptr, const uint8_t* master_base, uint64_t master_stride,
                              const uint8_t* shared_dev, int has_shared, FfnBatch* plan, uint32_t* stats,
                              hipStream_t st, const LaunchTiming& tm);
+
+// Whether launches on st are being captured into a graph.
+inline bool stream_capturing(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
 
 // Diagnostics.
 // Fills by the compute units: dst[i][0, bytes) <- src[i][0, bytes) for i < n, reading pinned host

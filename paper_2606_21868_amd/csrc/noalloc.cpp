@@ -93,7 +93,7 @@ extern "C" wisp_status wisp_route_topk_noalloc(const float* w_r_dev, const void*
   uint64_t* tagged = reinterpret_cast<uint64_t*>(base);
   float* logits = reinterpret_cast<float*>(base + kTagBytes);
   hipError_t e;
-  if (T <= 4) {
+  if (T <= 4 && !wisp::stream_capturing(st)) {   // (replays of a captured launch would repeat its tag)
     int dev = 0;
     (void)hipGetDevice(&dev);
     uint32_t tag = g_tag[dev].fetch_add(1, std::memory_order_relaxed) + 1;

@@ -41,3 +41,71 @@ def test_routing_against_oracle(T, N, d, x32):
         check_gates(run, got[0][0], got[0][1], ora_idx, ora_g, exempt)
     finally:
         run.close()
+
+
+def _route_run(T):
+    run = wisp.DecodeRun(BASE.with_(T=T, N=24, d=256), device=0, steps=1)
+    run.generate()
+    xs = [torch.randn(T, 256, device=run.dev, generator=torch.Generator(run.dev).manual_seed(i)).to(torch.bfloat16) for i in range(6)]
+    out = lambda: (torch.zeros((T, 2), dtype=torch.int32, device=run.dev), torch.zeros((T, 2), device=run.dev))
+
+    def eager(x):
+        idx, w = out()
+        run.ctx.route_topk(0, x, T, idx, w, np.zeros(T * 2, np.int32), run.stream)
+        run.stream.synchronize()
+        return idx, w
+    return run, xs, out, eager
+
+
+@pytest.mark.parametrize("T", [1, 4, 6, 8, 9])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_captured_routing_replays(T, noalloc):
+    # a graph's replays repeat the arguments of its launches, the one-launch router's tag among them
+    log(f"[case] captured routing T={T} {'noalloc' if noalloc else 'context'}")
+    run, xs, out, eager = _route_run(T)
+    try:
+        want = [eager(x) for x in xs]
+        x, (idx, w) = xs[0].clone(), out()
+
+        def call():
+            if noalloc:
+                wisp.route_topk_noalloc(run.wr_dev[0], x, wisp.BF16, T, 24, 256, 2, BASE.route, 1, 1, idx, w, run.stream)
+            else:
+                run.ctx.route_topk(0, x, T, idx, w, None, run.stream)
+        with torch.cuda.stream(run.stream):
+            call()   # (the context-free scratch clears its words once, outside the graph)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=run.stream):
+            call()
+        for i in (1, 2, 3, 4, 5, 0, 1, 2, 5, 4):
+            x.copy_(xs[i])
+            idx.fill_(-1)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(run.stream):
+                g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(idx, want[i][0]) and torch.equal(w, want[i][1]), i
+            if i == 3:   # its own work between replays (it leaves words of another tag, so not between all of them)
+                eager(xs[4])
+    finally:
+        run.close()
+
+
+@pytest.mark.parametrize("T", [2, 8])
+def test_routing_on_two_streams_in_turn(T):
+    # calls that wait for nothing, on two streams of one context, which share its tagged words
+    log(f"[case] routing on two streams T={T}")
+    run, xs, out, eager = _route_run(T)
+    try:
+        want = [eager(x) for x in xs]
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        got = [out() for _ in range(24)]
+        torch.cuda.synchronize()
+        for i, (idx, w) in enumerate(got):
+            run.ctx.route_topk(0, xs[i % 6], T, idx, w, None, streams[i // 3 % 2])
+        torch.cuda.synchronize()
+        for i, (idx, w) in enumerate(got):
+            assert torch.equal(idx, want[i % 6][0]) and torch.equal(w, want[i % 6][1]), i
+    finally:
+        run.close()
