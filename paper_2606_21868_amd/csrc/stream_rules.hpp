@@ -36,8 +36,8 @@ constexpr int kStreamMaxTokens = 15;
 // Up to 15 tokens (the alternative is the per-item kernels): fp8 weights, and bf16 from two tokens (one token has the
 // single-token kernels), in layers whose experts are large.  A wave goes through its token rows one after the other, each a
 // round trip for its inputs and a sum over the lanes: the weight stream has to be long against that.  Rows of one chunk
-// per lane never are (a sum over the lanes for every chunk), rows of two need 1.5 M weights a matrix, longer ones 1 M; half
-// of that or so where the per-item kernels read a row with eight lanes (an odd number of 128 bytes).
+// per lane never are (a sum over the lanes for every chunk), rows of two need 1.5 M weights a matrix, longer ones 1 M; 1.2 M
+// and 0.45 M where the per-item kernels read a row with eight lanes only (an odd number of 128 bytes).
 // us per launch pair, gate/up + down, streamed against per item.  Stream: fp8, one token (9 experts, d 7168, I 2048) 66.8
 // against 94.1; bf16, d 2048, I 768, seven tokens of 50 experts 71.6 against 92, two tokens of 8 19.4 against 18.8; 16 experts
 // by two rows: d 1024, I 1536 30.0 against 33.8; d 1536, I 768 22.2 against 25.2; d 1472, I 704 20.9 against 22.7; fp8, d 2048,
