@@ -33,7 +33,7 @@ Reported beside the throughput:
                  cap): tokens/s of a cold pass against T_roof = fault bytes / link + max(HBM bytes /
                  8 TB/s, FLOPs / 2.5 PFLOP/s), and the matrix-core rate of the grouped GEMMs in a
                  fully resident pass.
-The line printed holds the headline of each (a few KB); --detail FILE keeps everything measured.
+The line printed holds the headline of each (2 KB; sweep: cap, tokens/s, times zero-copy); --detail FILE keeps everything measured.
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--detail FILE]
 """
 from __future__ import annotations
@@ -656,10 +656,10 @@ def prefill_leg(wisp, torch, link, link_cu, passes=3):
 
 
 def pick(d, *keys):
-    """The named entries of d that it has (None if d is None), numbers to seven digits."""
+    """The named entries of d that it has (None if d is None), numbers to six digits."""
     if d is None:
         return None
-    num = lambda v: float(f"{v:.7g}") if isinstance(v, float) else v
+    num = lambda v: float(f"{v:.6g}") if isinstance(v, float) else v
     return {k: num(d[k]) for k in keys if k in d}
 
 
@@ -670,17 +670,17 @@ def summary(r):
     line["roofline"] = pick(r["roofline"], "bound", "achieved", "peak", "unit", "frac", "traffic", "kernel", "avg_launch_us",
                             "bytes_per_launch", "launches", "frac_of_read_floor")
     line["path_roofline"] = pick(r["path_roofline"], "frac", "roofline_tokens_per_s", "link_engine", "link_GBps_measured",
-                                 "faults_per_token", "fault_rate")
-    line["cpu_baseline"] = pick(r["cpu_baseline"], "value", "unit", "cores", "kind", "sample")
+                                 "faults_per_token")
+    line["cpu_baseline"] = pick(r["cpu_baseline"], "value", "unit", "cores", "kind")
     line["pager"] = r["pager"]
-    line["passes"] = {n: dict(pick(p, "tokens_per_s", "ms_per_step"), frac=pick(p["path_roofline"], "frac")["frac"])
+    line["passes"] = {n: dict(pick(p, "tokens_per_s"), frac=pick(p["path_roofline"], "frac")["frac"])
                       for n, p in r["passes"].items()}
     if r["prefill"]:
-        line["prefill"] = dict(pick(r["prefill"], "tokens_per_s", "pass_ms", "cap_per_layer", "faults"),
+        line["prefill"] = dict(pick(r["prefill"], "tokens_per_s", "pass_ms"),
                                frac=pick(r["prefill"]["roofline"], "frac")["frac"],
                                resident=pick(r["prefill"]["resident"], "tokens_per_s", "pass_ms"))
     if r["sweep"]:
-        line["sweep"] = [pick(c, "cap", "paged_tokens_per_s", "speedup_vs_zero_copy", "speedup_vs_bulk") for c in r["sweep"]]
+        line["sweep"] = [[c["cap"], *pick(c, "paged_tokens_per_s", "speedup_vs_zero_copy").values()] for c in r["sweep"]]
     if r["pageable_legs"]:
         line["pageable_legs"] = {n: dict(pick(v, "tokens_per_s"), frac=pick(v["path_roofline"], "frac")["frac"])
                                  for n, v in r["pageable_legs"].items()}

@@ -8,7 +8,9 @@ LEG = {f"leg_{i}": [0.123456789] * 50 for i in range(40)}
 ROOF = dict(frac=0.9123456789, roofline_tokens_per_s=80.0, link_engine="compute_units", link_GBps_measured=56.6, t_roof_s=1.0,
             faults_per_token=68.0, fault_rate=0.2, side=LEG)
 FULL = dict(metric="m", value=74.123456789, unit="tokens/s", n_gpus=1, steps=20, warmup=5, ms_per_step=13.5, higher_is_better=True,
-            scaling="weak", vs_baseline=None, dtype="bf16", data="synthetic", config=dict(layers=48, batch=1),
+            scaling="weak", vs_baseline=None, dtype="bf16", data="synthetic",
+            config=dict(workload="x" * 150, layers=48, d_model=2048, d_ff=768, experts=128, top_k=8, batch=1,
+                        expert_budget_bytes=14495514624, cap_per_layer=32, expert_blob_bytes=9437184),
             roofline=dict(bound="hbm", achieved=4000.0, peak=8000.0, unit="GB/s", frac=0.5, traffic=None, traffic_detail=LEG),
             path_roofline=ROOF, cpu_baseline=dict(value=1.04, unit="tokens/s", cores=16, kind="oracle", sample="16 layer-steps"),
             pager="device", kernel_timing="gateup",
@@ -23,12 +25,12 @@ FULL = dict(metric="m", value=74.123456789, unit="tokens/s", n_gpus=1, steps=20,
 
 def test_line_is_short_and_holds_the_contract():
     line = json.dumps(bench.summary(FULL))
-    assert len(line) < 4000 and "\n" not in line
+    assert len(line) < 2000 and "\n" not in line
     got = json.loads(line)
     for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
               "dtype", "data", "config"):
         assert got[k] == FULL[k]
-    assert got["path_roofline"]["frac"] == 0.9123457 and got["sweep"][2]["cap"] == 32
+    assert got["path_roofline"]["frac"] == 0.912346 and got["sweep"][2] == [32, 40.0, 3.0]
 
 
 def test_line_without_the_side_legs():
